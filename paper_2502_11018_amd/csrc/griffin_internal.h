@@ -36,6 +36,8 @@ struct PackShape {
   int swiglu;   // 1: rows [0, n_out) are gate rows, [n_out, 2 n_out) up rows; a wave's blocks
                 // [0, nb/2) are gate blocks, block b + nb/2 the up rows of block b
   int n_out;    // SwiGLU output columns (d_ff)
+  int group_major;  // 1: a stream's K steps are contiguous (block (t, q, b) at ((q * len + t) * nb + b) * 2048),
+                    // the layout of gemm_rows.hip; 0: step-major over the streams
 };
 
 __host__ __device__ inline long long packed_elems(const PackShape& p) {
@@ -61,13 +63,14 @@ struct GemmArgs {
   int epi, nb, wn, pf;       // kernel variant
   int n_wgs, splits, len;    // launch shape (matches the weight packing): splits = K slices
   int kslices;               // K slices merged inside one workgroup (output splits = splits / kslices)
-  int tg;                    // 64-row tiles per workgroup sharing each weight fragment (1 or 4)
+  // gemm_rows.hip only (its len is the K steps of one split, n_wgs the column tiles)
+  int ks;                    // K steps of the matrix
+  int rows_wm, rows_wn;      // workgroup tile: 64 rows_wm rows x 128 rows_wn columns
   int N;                     // output columns (SwiGLU: d_ff)
   int m_tiles;               // 64-row activation tiles
   const uint16_t* X;         // packed activations
   int x_ks;                  // K steps per activation tile
   int xlo;                   // 1: activations as bf16 hi + lo (fp32-grade); 0: the bf16 hi part alone
-  int nt;                    // LM head: 1 = non-temporal weight loads (one row tile: each weight read once)
   int x_etiles;              // MoE: activation tiles per expert (0 for dense)
   const int32_t* count;      // MoE: [E] valid rows per expert; NULL = m_tiles * 64
   const uint16_t* W;         // packed weights (+ e * w_estride)
@@ -167,6 +170,7 @@ struct AttnArgs {
 
 // launchers (return hipGetLastError())
 hipError_t launch_gemm(const GemmArgs& a, int experts, hipStream_t s);
+hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
 hipError_t launch_pack_weight(const uint16_t* src, int rows, int K, const PackShape& p, uint16_t* dst,
                               hipStream_t s);
 hipError_t launch_embed(const uint16_t* embed, const int32_t* token, int rows, int d, float* x, hipStream_t s);

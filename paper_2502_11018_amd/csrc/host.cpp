@@ -32,12 +32,20 @@ int cdiv(int x, int m) { return (x + m - 1) / m; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Launch of gemm_rows.hip for one step: workgroup tile 64 wm rows x 128 wn
+// columns, `splits` K splits of `len` steps.
+struct RowsLaunch {
+  int wm = 0, wn = 0, splits = 1, len = 0;
+};
+
 // Launch shape of one weight matrix (fixed at init; the packing follows it).
 struct GemmPlan {
   int epi = 0, nb = 1, wn = 4, pf = 4;
-  int tg = 1;       // 64-row tiles per workgroup
   int kslices = 1;  // K slices merged inside a workgroup (shape.splits / kslices output splits)
-  int out_splits() const { return shape.splits / kslices; }
+  // several row tiles (gemm_rows.hip): the launch for a step of t + 1 tiles
+  std::vector<RowsLaunch> rows_for;
+  bool by_rows() const { return !rows_for.empty(); }
+  int out_splits(int m_tiles) const { return by_rows() ? rows_for[m_tiles - 1].splits : shape.splits / kslices; }
   int n_out = 0;   // output columns
   int rows = 0;    // weight rows (SwiGLU: 2 * n_out)
   int K = 0, ks = 0, ks_pad = 0;
@@ -45,57 +53,58 @@ struct GemmPlan {
   long long elems = 0;  // packed elements of one matrix (one expert)
 };
 
-// m_tiles: the most 64-row tiles a step of the context can have.  With
-// several tiles (batched rows) the GEMMs approach the MFMA bound, and each
-// weight fragment is shared between two 64-row tiles per workgroup:
-//  * gate/up: every wave holds two gate and the matching two up blocks, so
-//    each activation fragment read from LDS feeds four weight blocks (the
-//    LDS reads, not HBM, bound these launches);
-//  * wide_tiles (QKV, O and down): two 32-column blocks per wave with three
-//    pipeline stages.
-// Measured at 8 x 61 rows (Llama-3-8B shapes, per launch): gate/up 254 ->
-// 222 us; with the wide form down 122 -> 113 us, O 56 -> 45 us, QKV about
-// 70 -> 60 us.  The LM head gained little and keeps one tile per workgroup.
-GemmPlan plan_gemm(int epi, int n_out, int K, int experts = 1, int m_tiles = 1, bool wide_tiles = false) {
+// Tile shape and K splits of a gemm_rows launch over m_tiles row tiles: the
+// least estimated time.  Measured per K step and 64 x 128 tile of a workgroup
+// (Llama-3-8B shapes, 128 to 512 rows): 0.37 us in the 256- and 128-row x 256-column
+// shapes, 0.40 us in the 128-row x 128-column and 0.43 in the 64-row one (more operand bytes per
+// MFMA), in whole rounds of 256 workgroups; 8 us per round for the launch, the
+// ring's fill and the slice merge; partial sums at about 3.3 TB/s for the
+// write and the consumer's read together; and never faster than the weight
+// stream at 4.2 TB/s.
+RowsLaunch plan_rows(int epi, int groups, int ks, int n_cols, int m_tiles) {
+  static const int shapes[4][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 2}};
+  RowsLaunch best;
+  double best_t = 1e30;
+  for (const auto& sh : shapes) {
+    const int wm = sh[0], wn = sh[1];
+    const int tiles = cdiv(m_tiles, wm) * (groups / wn);
+    const int most = epi == EPI_STORE ? std::min(16, std::max(1, ks / 4)) : 1;
+    for (int want = 1; want <= most; ++want) {
+      const int len = cdiv(ks, want), splits = cdiv(ks, len);
+      const double step = wm * wn * (wn * wm >= 4 ? 0.37 : wm == 2 ? 0.40 : 0.43);  // us per K step
+      double t = cdiv(tiles * splits, 256) * (len * step + 8.0);
+      t = std::max(t, (double)groups * ks * 16384.0 / 4.2e6);
+      if (epi == EPI_STORE) t += splits * m_tiles * 64.0 * n_cols * 4.0 / 3.3e6;
+      if (t < best_t) {
+        best_t = t;
+        best.wm = wm;
+        best.wn = wn;
+        best.splits = splits;
+        best.len = len;
+      }
+    }
+  }
+  return best;
+}
+
+// m_tiles: the most 64-row tiles a step of the context can have.  With one
+// tile the weight stream bounds the GEMMs (gemm.hip); with several the matrix
+// cores do (gemm_rows.hip).  Experts see few rows each and keep gemm.hip.
+GemmPlan plan_gemm(int epi, int n_out, int K, int experts = 1, int m_tiles = 1) {
   GemmPlan p;
   p.epi = epi;
   p.n_out = n_out;
   p.K = K;
   p.ks = cdiv(K, 64);
-  if (m_tiles >= 2 && experts == 1 && epi == EPI_SWIGLU) {
-    p.tg = 2;
-    p.kslices = 1;
-    p.pf = 3;
+  if (m_tiles >= 2 && experts == 1) {
     p.nb = 4;
-    p.wn = 4;
-    p.rows = 2 * n_out;
-    const int n_wgs = cdiv(cdiv(n_out, 32 * (p.nb / 2)), p.wn);
+    p.wn = 1;
+    p.rows = epi == EPI_SWIGLU ? 2 * n_out : n_out;
+    const int groups = round_up(cdiv(p.rows, 128), 2);  // any tile width divides them
     p.ks_pad = p.ks;
-    p.shape = PackShape{p.nb, p.wn, 1, p.ks, n_wgs, 1, n_out};
+    p.shape = PackShape{p.nb, p.wn, 1, p.ks, groups, epi == EPI_SWIGLU ? 1 : 0, n_out, 1};
     p.elems = packed_elems(p.shape);
-    return p;
-  }
-  if (m_tiles >= 2 && experts == 1 && epi == EPI_STORE && wide_tiles) {
-    // two row tiles per workgroup, two column blocks per wave and three
-    // pipeline stages: four blocks with two stages (the register budget's
-    // other choice) wait a full memory latency at every step (long-context
-    // step 27.1 -> 26.1 ms for O and down, 25.3 ms with QKV in this form)
-    p.tg = 2;
-    p.kslices = 1;
-    p.pf = 3;
-    p.nb = 2;
-    p.wn = 4;
-    p.rows = n_out;
-    const int n_wgs = cdiv(cdiv(n_out, 32 * p.nb), p.wn);
-    // K splits: about 256 workgroups in all (the grid holds round_up(n_wgs,
-    // 8) workgroups per pair of row tiles), at least 4 K steps per split;
-    // 512 measured slower for both matrices
-    const int per_split = round_up(n_wgs, 8) * cdiv(m_tiles, 2);
-    const int splits = std::max(1, std::min(16, std::min(p.ks / 4, 256 / per_split)));
-    const int len = cdiv(p.ks, splits);
-    p.ks_pad = len * splits;
-    p.shape = PackShape{p.nb, p.wn, splits, len, n_wgs, 0, n_out};
-    p.elems = packed_elems(p.shape);
+    for (int t = 1; t <= m_tiles; ++t) p.rows_for.push_back(plan_rows(epi, groups, p.ks, n_out, t));
     return p;
   }
   int splits = 1;
@@ -151,7 +160,7 @@ GemmPlan plan_gemm(int epi, int n_out, int K, int experts = 1, int m_tiles = 1, 
   const int len = cdiv(p.ks, splits);
   p.ks_pad = len * splits;
   p.pf = len >= 8 ? (p.kslices > 1 ? 3 : 4) : 2;
-  p.shape = PackShape{p.nb, p.wn, splits, len, n_wgs, epi == EPI_SWIGLU ? 1 : 0, n_out};
+  p.shape = PackShape{p.nb, p.wn, splits, len, n_wgs, epi == EPI_SWIGLU ? 1 : 0, n_out, 0};
   p.elems = packed_elems(p.shape);
   return p;
 }
@@ -297,18 +306,27 @@ GemmArgs gemm_args(const GemmPlan& p, const uint16_t* X, int x_ks, const uint16_
   a.n_wgs = p.shape.n_wgs;
   a.splits = p.shape.splits;
   a.kslices = p.kslices;
-  a.tg = p.tg;
   a.len = p.shape.len;
   a.N = p.n_out;
   a.m_tiles = m_tiles;
-  // each weight read once (one row tile): stream the LM head past the caches;
-  // with several tiles their re-reads of a fragment are served by L2
-  a.nt = p.epi == EPI_ARGMAX && m_tiles == 1 ? 1 : 0;
   a.X = X;
   a.x_ks = x_ks;
   a.xlo = xlo ? 1 : 0;
   a.W = W;
+  if (p.by_rows()) {
+    const RowsLaunch& r = p.rows_for[m_tiles - 1];
+    a.rows_wm = r.wm;
+    a.rows_wn = r.wn;
+    a.n_wgs = p.shape.n_wgs / r.wn;
+    a.splits = r.splits;
+    a.len = r.len;
+    a.ks = p.ks;
+  }
   return a;
+}
+
+hipError_t launch_plan(const GemmPlan& p, const GemmArgs& a, int experts, hipStream_t s) {
+  return p.by_rows() ? launch_gemm_rows(a, s) : launch_gemm(a, experts, s);
 }
 
 // Event pair for one timed launch (grown on demand, reused after each read).
@@ -382,11 +400,11 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
       a.ldo = c->qkv_n;
       a.out_split_stride = ps * c->qkv_n;
       a.stamp = stamp_slot(c, GRIFFIN_KC_QKV);
-      LAUNCH(GRIFFIN_KC_QKV, launch_gemm(a, 1, s));
+      LAUNCH(GRIFFIN_KC_QKV, launch_plan(c->p_qkv, a, 1, s));
     }
     uint16_t* kc = c->k_cache + (size_t)l * layer_kv;
     uint16_t* vc = c->v_cache + (size_t)l * layer_kv;
-    LAUNCH(GRIFFIN_KC_ROPE, launch_qkv_rope(c->parts, c->p_qkv.out_splits(), ps * c->qkv_n, c->meta, c->rope_inv,
+    LAUNCH(GRIFFIN_KC_ROPE, launch_qkv_rope(c->parts, c->p_qkv.out_splits(m_tiles), ps * c->qkv_n, c->meta, c->rope_inv,
                                             d.n_q_heads, d.n_kv_heads, d.head_dim, d.max_tree, B, d.kv_capacity,
                                             c->q, c->q_lo, kc, vc, c->tree, s));
     if (c->kv_only && l == d.n_layers - 1) return GRIFFIN_OK;
@@ -421,11 +439,11 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
       a.ldo = d.d_model;
       a.out_split_stride = ps * d.d_model;
       a.stamp = stamp_slot(c, GRIFFIN_KC_O);
-      LAUNCH(GRIFFIN_KC_O, launch_gemm(a, 1, s));
+      LAUNCH(GRIFFIN_KC_O, launch_plan(c->p_o, a, 1, s));
     }
     ResidualAdd add_o{};
     add_o.parts = c->parts;
-    add_o.n_parts = c->p_o.out_splits();
+    add_o.n_parts = c->p_o.out_splits(m_tiles);
     add_o.part_stride = ps * d.d_model;
     Router route{};
     if (c->E > 1) {  // MoE: the MLP norm also routes every row
@@ -454,16 +472,16 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
       g.act = c->act;
       g.act_ks = c->p_down.ks_pad;
       g.stamp = stamp_slot(c, GRIFFIN_KC_GATE_UP);
-      LAUNCH(GRIFFIN_KC_GATE_UP, launch_gemm(g, 1, s));
+      LAUNCH(GRIFFIN_KC_GATE_UP, launch_plan(c->p_gu, g, 1, s));
       GemmArgs dn = gemm_args(c->p_down, c->act, c->p_down.ks_pad, c->pk_down[l], m_tiles, !c->act_bf16);
       dn.out = c->parts;
       dn.ldo = d.d_model;
       dn.out_split_stride = ps * d.d_model;
       dn.stamp = stamp_slot(c, GRIFFIN_KC_DOWN);
-      LAUNCH(GRIFFIN_KC_DOWN, launch_gemm(dn, 1, s));
+      LAUNCH(GRIFFIN_KC_DOWN, launch_plan(c->p_down, dn, 1, s));
       add_down = ResidualAdd{};
       add_down.parts = c->parts;
-      add_down.n_parts = c->p_down.out_splits();
+      add_down.n_parts = c->p_down.out_splits(m_tiles);
       add_down.part_stride = ps * d.d_model;
     } else {
       const int xe_tiles = Mpad / 64;  // the routing norm filled count, slot and the experts' tiles
@@ -491,7 +509,7 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
       add_down.slot = c->slot;
       add_down.slot_w = c->route_w;
       add_down.top_k = c->topk;
-      add_down.n_parts = c->p_down.out_splits();
+      add_down.n_parts = c->p_down.out_splits(m_tiles);
       add_down.part_stride = (long long)c->E * Mpad * d.d_model;
     }
   }
@@ -513,7 +531,7 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
     a.ld_logits = d.vocab;
     a.logit_rows = rows;
     a.stamp = stamp_slot(c, GRIFFIN_KC_LM_HEAD);
-    LAUNCH(GRIFFIN_KC_LM_HEAD, launch_gemm(a, 1, s));
+    LAUNCH(GRIFFIN_KC_LM_HEAD, launch_plan(c->p_lm, a, 1, s));
   }
   if (c->front) return GRIFFIN_OK;  // a draft pass: the caller reads the logits
   LAUNCH(GRIFFIN_KC_OTHER, launch_argmax_reduce(c->pmax, c->pmax2, c->pidx, c->pnan, lm_parts, lm_parts, rows,
@@ -623,10 +641,10 @@ DraftArgs draft_args(griffin_draft* dc, griffin_ctx* c) {
   a.h = dc->h;
   a.x = c->x;
   a.parts = dc->parts;
-  a.n_parts_m = dc->p_m.out_splits();
-  a.n_parts_u = dc->p_u.out_splits();
-  a.n_parts_d = dc->p_d.out_splits();
-  a.n_parts_h = dc->p_h.out_splits();
+  a.n_parts_m = dc->p_m.out_splits(mpad / 64);
+  a.n_parts_u = dc->p_u.out_splits(mpad / 64);
+  a.n_parts_d = dc->p_d.out_splits(mpad / 64);
+  a.n_parts_h = dc->p_h.out_splits(mpad / 64);
   a.stride_m = (long long)mpad * dc->d;
   a.stride_u = (long long)mpad * dc->e;
   a.stride_d = (long long)mpad * dc->d;
@@ -661,7 +679,7 @@ hipError_t draft_gemm(griffin_draft* dc, griffin_ctx* c, const GemmPlan& p, cons
   a.out = dc->parts;
   a.ldo = N;
   a.out_split_stride = (long long)mpad * N;
-  return launch_gemm(a, 1, s);
+  return launch_plan(p, a, 1, s);
 }
 
 }  // namespace
@@ -782,17 +800,17 @@ int griffin_verify_init(const griffin_model_desc* desc, const griffin_weights* w
   }
   c->comb_slots = c->attn_sp;
   const int max_tiles = c->Mpad / 64;
-  c->p_qkv = plan_gemm(EPI_STORE, c->qkv_n, d.d_model, 1, max_tiles, true);
-  c->p_o = plan_gemm(EPI_STORE, d.d_model, c->attn_w, 1, max_tiles, true);
+  c->p_qkv = plan_gemm(EPI_STORE, c->qkv_n, d.d_model, 1, max_tiles);
+  c->p_o = plan_gemm(EPI_STORE, d.d_model, c->attn_w, 1, max_tiles);
   c->p_gu = plan_gemm(EPI_SWIGLU, d.d_ff, d.d_model, c->E, max_tiles);
-  c->p_down = plan_gemm(EPI_STORE, d.d_model, d.d_ff, c->E, max_tiles, true);
+  c->p_down = plan_gemm(EPI_STORE, d.d_model, d.d_ff, c->E, max_tiles);
   c->p_lm = plan_gemm(EPI_ARGMAX, d.vocab, d.d_model, 1, max_tiles);
   c->xd_ks = std::max({c->p_qkv.ks_pad, c->p_gu.ks_pad, c->p_lm.ks_pad});
   const long long Mp = c->Mpad;
   const long long tiles = Mp / 64;
-  c->parts_elems = Mp * std::max({(long long)c->p_qkv.out_splits() * c->qkv_n,
-                                  (long long)c->p_o.out_splits() * d.d_model,
-                                  (long long)c->p_down.out_splits() * d.d_model});
+  for (const GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_down})
+    for (int t = 1; t <= max_tiles; ++t)
+      c->parts_elems = std::max(c->parts_elems, 64LL * t * p->out_splits(t) * p->n_out);
   const int qrows = c->qblocks * 32;
 
 #define ALLOC(ptr, n)                              \
@@ -838,7 +856,7 @@ int griffin_verify_init(const griffin_model_desc* desc, const griffin_weights* w
     ALLOC(c->router_logits, (long long)d.n_layers * d.max_batch * d.max_tree * c->E);
     ALLOC(c->count, c->E);
     ALLOC(c->slot, Mp * c->topk);
-    ALLOC(c->yslots, (long long)c->p_down.out_splits() * c->E * Mp * d.d_model);
+    ALLOC(c->yslots, (long long)c->p_down.out_splits(max_tiles) * c->E * Mp * d.d_model);
     ALLOC(c->xe, (long long)c->E * tiles * c->xd_ks * XPACK_STEP);
   }
 #undef ALLOC
@@ -1542,7 +1560,7 @@ int griffin_draft_init(const griffin_model_desc* desc, int32_t tgf_dim, float ln
   dc->p_h = plan_gemm(EPI_STORE, 2 * d, d, 1, tiles);
   long long parts = 0;
   for (const GemmPlan* p : {&dc->p_m, &dc->p_u, &dc->p_d, &dc->p_h})
-    parts = std::max(parts, (long long)p->out_splits() * mpad * p->n_out);
+    for (int t = 1; t <= tiles; ++t) parts = std::max(parts, 64LL * t * p->out_splits(t) * p->n_out);
   auto alloc = [&](void** p, size_t bytes) {
     if (hipMalloc(p, std::max<size_t>(bytes, 256)) != hipSuccess) return false;
     dc->allocs.push_back(*p);
