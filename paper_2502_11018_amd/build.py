@@ -22,6 +22,12 @@ LIBNAME = "libgriffin_verify.so"
 ARCH = "gfx950"
 
 
+# Accumulators in the vector registers although a wave holds more than 256 in
+# all: with them in the accumulation registers every score costs a move before
+# the softmax can read it.
+FILE_FLAGS = {"attention.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+
+
 def hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", shutil.which("hipcc")):
         if cand and os.path.exists(cand):
@@ -53,7 +59,7 @@ def build(verbose: bool = False) -> str:
     procs = []
     for src in sources():
         obj = os.path.join(objdir, os.path.basename(src) + ".o")
-        cmd = [hipcc(), *compile_flags(), "-c", src, "-o", obj]
+        cmd = [hipcc(), *compile_flags(), *FILE_FLAGS.get(os.path.basename(src), []), "-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

@@ -6,12 +6,14 @@
 // keys of each node (its ancestors) are added by attn_combine in fp32, from
 // fp32 copies of the tree K/V, while it merges the prefix splits.
 //
-// tree_attention_kernel: a workgroup handles one (sequence, KV head, block of
-// 32 tree rows, prefix split, chunk of NW query heads of that KV head's
-// group).  Its NW waves share every 32-key block of K and V, which the
-// workgroup stages once into an LDS ring with global_load_lds_dwordx4 (each
-// wave issues an equal share of the block's 1 KB pieces), so the cache is read
-// once per head group rather than once per head.
+// tree_attention_kernel: a workgroup handles one (sequence, KV head, prefix
+// split) for NW of the KV head's row tiles.  A row tile is 32 tree rows of one
+// query head, or, where a sequence's rows of the whole head group fit one tile
+// (max_tree * group <= 32: short chains), all of them (PACK).  The NW waves,
+// one row tile each, share every 32-key block of K and V, which the workgroup
+// stages once into an LDS ring with global_load_lds_dwordx4 (each wave issues
+// an equal share of the block's 1 KB pieces), so the cache is read once per
+// workgroup rather than once per head.
 //
 // Per 32-key block each wave computes S^T = K Q^T and O^T += V^T P^T with
 // v_mfma_f32_32x32x16_bf16, so that each lane owns one query row (column of
@@ -31,27 +33,20 @@
 // Scores are kept in the log2 domain (scaled by log2(e)/sqrt(dh)) and exp2 is
 // used throughout; masked keys contribute exactly zero.
 
-#include <type_traits>
-
 #include "device_common.h"
 #include "griffin_internal.h"
 
 namespace griffin {
 
-// LEAN: two workgroups per CU (at most 256 registers per lane): no
-// cross-block software pipeline in a wave, K and V fragments read from LDS
-// half a block at a time; the second wave of each SIMD hides what the first
-// one waits on.  Chosen when a step has enough key-split units to fill two
-// workgroups per CU (long prefixes, several sequences).
-template <int DH, int NW, bool RAGGED, bool LEAN>
-__global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(AttnArgs a) {
+template <int DH, int NW, bool RAGGED, bool PACK>
+__global__ __launch_bounds__(64 * NW, 1) void tree_attention_kernel(AttnArgs a) {
   constexpr int CH = DH / 64;          // 64-dim chunks of Q/K per lane pair
   constexpr int DB = DH / 32;          // 32-dim blocks of the output
   constexpr int KP = CH * 4;           // 1 KB pieces of a K block
   constexpr int PIECES = KP + DB * 2;  // K and V pieces of one 32-key block
   constexpr int PPW = PIECES / NW;     // pieces each wave stages per block
   constexpr int D = ATTN_RING;         // ring slots
-  static_assert(PIECES % NW == 0 && PPW * (D - 2) < 64, "ring shape");
+  static_assert(PIECES % NW == 0 && PPW * (D - 1) < 64 && (!PACK || NW == 1), "ring shape");
   __shared__ u32x4 ring[D][PIECES][64];
 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -63,8 +58,8 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(A
   // workgroup of one (unit, KV head) gets the same id % 8 and the K/V blocks
   // it re-reads are shared through that XCD's L2.
   const int G = a.Hq / a.Hkv;
-  const int chunks = (G + NW - 1) / NW;
-  const int per_unit = chunks * a.qblocks;
+  const int tiles = PACK ? 1 : G * a.qblocks;  // row tiles of a KV head: tile qb * G + head
+  const int per_unit = (tiles + NW - 1) / NW;
   const int id = blockIdx.x;
   const int rest = id >> 3;
   const int u_raw = (rest / per_unit) * 8 + (id & 7);
@@ -74,9 +69,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(A
   // once
   const bool unit_live = u_raw < a.units * a.Hkv;  // uniform over the workgroup
   const int u = unit_live ? u_raw : 0;
-  const int within = rest % per_unit;
-  const int qb = within % a.qblocks;
-  const int chunk = within / a.qblocks;
+  const int tile0 = rest % per_unit * NW;  // first row tile of the workgroup
   const int hk = u % a.Hkv;
   // RAGGED: the unit comes from the step's split table; else every sequence
   // has a.sp splits and unit j is split j % sp of sequence j / sp
@@ -88,17 +81,21 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(A
     ent = make_int4((u / a.Hkv / a.sp) | ((u / a.Hkv % a.sp) << 16), a.sp, 0, 0);
   }
   const int b = ent.x & 0xffff, split = ent.x >> 16, nsplit = ent.y;
-  const int gh = chunk * NW + w;           // head within the group
-  const bool head_live = gh < G;           // wave-uniform
-  const int hq = hk * G + (head_live ? gh : 0);
+  const bool tile_live = tile0 + w < tiles;  // wave-uniform
+  const int tile_w = tile_live ? tile0 + w : tile0;
+  const int qb = PACK ? 0 : tile_w / G;
   const int qrows = a.qblocks * 32;
+  // row `col` of the tile: head gh of the group, node qi (PACK: the group's
+  // heads one after the other, max_tree rows each)
+  auto row_head = [&](int r) { return PACK ? r / a.max_tree : tile_w % G; };
+  auto row_node = [&](int r) { return PACK ? r % a.max_tree : qb * 32 + r; };
 
   // Q^T operand (B): lane (col = query row, hh = k-group), 32 dims per chunk;
   // split bf16, so S = K (q_hi + q_lo).  Loaded before the per-sequence
   // metadata is known (rows past the tree hold stale values and are never
   // written out; the row index stays inside the sequence's max_tree rows).
-  const int qi = qb * 32 + col;
-  const int qr = b * a.max_tree + min(qi, a.max_tree - 1);
+  const int qr = b * a.max_tree + min(row_node(col), a.max_tree - 1);
+  const int hq = hk * G + min(row_head(col), G - 1);
   u32x4 qf[2][CH][4];
   {
     const long long qo = ((long long)qr * a.Hq + hq) * DH + 32 * hh;
@@ -140,22 +137,23 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(A
       goff[p] = 2u * ((32 * d + col) * 32 + 16 * hh + 8 * t);
     }
   }
+  auto issue_piece = [&](int slot, int kb, int p) {
+    const int pc = wu * PPW + p;
+    const char* blk = reinterpret_cast<const char*>((pc < KP ? kbase : vbase) + (long long)kb * 32 * DH);
+    __builtin_amdgcn_global_load_lds((const void*)(blk + goff[p]), (lds_void*)&ring[slot][pc][0], 16, 0, 0);
+  };
   auto issue = [&](int slot, int kb) {
 #pragma unroll
-    for (int p = 0; p < PPW; ++p) {
-      const int pc = wu * PPW + p;
-      const char* blk = reinterpret_cast<const char*>((pc < KP ? kbase : vbase) + (long long)kb * 32 * DH);
-      __builtin_amdgcn_global_load_lds((const void*)(blk + goff[p]), (lds_void*)&ring[slot][pc][0], 16, 0, 0);
-    }
+    for (int p = 0; p < PPW; ++p) issue_piece(slot, kb, p);
   };
-  // The first D - 1 blocks go out as soon as the prefix length is known (the
+  // The first D blocks go out as soon as the prefix length is known (the
   // longest latency of the prologue), before the check for live rows: a
   // workgroup without live rows lets them land and leaves.
   if (nb > 0) {
 #pragma unroll
-    for (int i = 0; i < D - 1; ++i) issue(i, kb0 + min(i, nb - 1));
+    for (int i = 0; i < D; ++i) issue(i, kb0 + min(i, nb - 1));
   }
-  if (!unit_live || qb * 32 >= n_nodes) {  // no unit, or no live query rows in this block (uniform)
+  if (!unit_live || (!PACK && tile0 / G * 32 >= n_nodes)) {  // no unit, or no live query rows (uniform)
     wait_vmcnt_lds<0>();
     return;
   }
@@ -170,181 +168,162 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(A
   // and the merge recomputes that split exactly.  So p needs no clamp: only
   // flagged rows can overflow, and a NaN score stays NaN (a clamp cost 0.8 us
   // per launch, the running maximum 10 us at 16384 keys per sequence).
+  // l_run sums the lane's own 16 keys of every block; the two halves of a row
+  // meet once, after the loop.
   float m_ref = -INFINITY, l_run = 0.f;
   f32x16 oacc[DB];
-
-  // QK: S^T = K Q^T for the block in `slot` (rows: keys, cols: queries),
-  // q = q_hi + q_lo.
-  auto qk = [&](int slot) {
-    // all K fragments are read before the first MFMA, so the LDS latency is
-    // paid once per block (LEAN: once per 64-dim chunk)
-    constexpr int KR = LEAN ? 4 : CH * 4;  // K fragments held at once
-    f32x16 sacc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
-#pragma unroll
-    for (int c0 = 0; c0 < CH * 4; c0 += KR) {
-      u32x4 kf[KR];
-#pragma unroll
-      for (int x = 0; x < KR; ++x) kf[x] = ring[slot][c0 + x][lane];
-#pragma unroll
-      for (int x = 0; x < KR; ++x)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[x]), as_bf16x8(qf[h][(c0 + x) / 4][(c0 + x) % 4]),
-                                                         sacc, 0, 0, 0);
-    }
-    return sacc;
-  };
-
-  // SV: softmax of one block's scores and O^T += V^T P^T.  TAIL is true only
-  // for the last prefix block when P is not a multiple of 32: its keys at or
-  // beyond P get probability 0 and their V is zeroed (those slots hold tree
-  // or stale values), with branch-free selects.  `first` marks the block
-  // that sets m_ref.
-  auto sv = [&](auto tail, const f32x16& sacc, int slot, int kb, bool first) {
-    constexpr bool TAIL = decltype(tail)::value;
-    const int key0 = kb * 32;
-    // mask (this lane: keys key0 + 16 hh + r); the log2-domain scale is
-    // applied inside the exponent (scale > 0 commutes with max)
-    float s[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      s[r] = sacc[r];
-      if constexpr (TAIL) s[r] = (key0 + 16 * hh + r < P) ? s[r] : -INFINITY;
-    }
-    if (first) {  // wave-uniform
-      float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
-      mx = fmaxf(mx, fmaxf(fmaxf(fmaxf(s[8], s[9]), fmaxf(s[10], s[11])),
-                           fmaxf(fmaxf(s[12], s[13]), fmaxf(s[14], s[15]))));
-      m_ref = fmaxf(mx, __shfl_xor(mx, 32, 64)) * a.scale_log2;
-    }
-    float p[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], a.scale_log2, -m_ref));
-    const float psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])) +
-                       (((p[8] + p[9]) + (p[10] + p[11])) + ((p[12] + p[13]) + (p[14] + p[15])));
-    l_run += psum + __shfl_xor(psum, 32, 64);
-
-    // O^T += V^T P^T, P as split bf16 (p_hi + p_lo); all V fragments are
-    // read before the first MFMA (LEAN: those of each 16-key half)
-    constexpr int VT = LEAN ? 1 : 2;  // 16-key halves of V held at once
-    u32x4 vfr[2][DB];
-#pragma unroll
-    for (int t = 0; t < VT; ++t)
-#pragma unroll
-      for (int d = 0; d < DB; ++d) vfr[t][d] = ring[slot][KP + d * 2 + t][lane];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      if (LEAN && t == 1) {
-#pragma unroll
-        for (int d = 0; d < DB; ++d) vfr[0][d] = ring[slot][KP + d * 2 + 1][lane];
-      }
-      const int tv = LEAN ? 0 : t;  // where this half's V fragments are held
-      u32x4 pf[2];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const Hilo2 hl = pack_hilo2(p[8 * t + 2 * q], p[8 * t + 2 * q + 1]);
-        pf[0][q] = hl.hi;
-        pf[1][q] = hl.lo;
-      }
-      uint32_t keep[4];
-      if constexpr (TAIL) {
-        const int kfirst = key0 + 16 * hh + 8 * t;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)  // bf16 element 2q is the low half of dword q
-          keep[q] = (kfirst + 2 * q < P ? 0x0000ffffu : 0u) | (kfirst + 2 * q + 1 < P ? 0xffff0000u : 0u);
-      }
-#pragma unroll
-      for (int d = 0; d < DB; ++d) {
-        u32x4 vf = vfr[tv][d];
-        if constexpr (TAIL) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) vf[q] &= keep[q];
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf), as_bf16x8(pf[h]), oacc[d], 0, 0, 0);
-      }
-    }
-  };
-
-  // Ring pipeline over the split's blocks (same structure as the GEMM's),
-  // software-pipelined by one block: step i computes the scores of block
-  // i + 1 (matrix cores) before the softmax and P V of block i (vector ALU,
-  // then matrix cores), so the two overlap.  At the top of step i every wave
-  // waits for its own DMA pieces of block i + 1 (vector-memory counters
-  // retire in issue order) and for its LDS reads of earlier slots; the
-  // barrier then publishes block i + 1 and frees the slot of block i - 1,
-  // which block i + D - 1 overwrites.  Issues past the last block re-read it
-  // into slots that are never consumed; every DMA has landed before the waves
-  // leave.  The loop is unrolled by the ring depth (slot indices are
-  // compile-time constants) and the split's last block, the only one that
-  // can be partial (the TAIL form), is handled after it: with one path
-  // through the loop body the accumulators stay in place and the only
-  // vector-memory waits are the ones written here.
-  static_assert(D >= 3, "one block of scores runs ahead of the ring");
-  const int nfull = (kb0 + nb) * 32 <= P ? nb : nb - 1;
 #pragma unroll
   for (int d = 0; d < DB; ++d)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[d][r] = 0.f;
-  if (nb > 0 && LEAN) {
-    // one block per step: wait for block i (blocks i+1 .. i+D-2 stay in
-    // flight), publish it, refill the slot of block i - 1, then scores,
-    // softmax and P V of block i
-    auto step = [&](auto tail, int u, int i) {
-      wait_vmcnt_lds<(D - 2) * PPW>();
-      __builtin_amdgcn_s_barrier();
-      issue((u + D - 1) % D, kb0 + min(i + D - 1, nb - 1));
-      const f32x16 sc = qk(u);
-      sv(tail, sc, u, kb0 + i, i == 0);
-    };
-    int base = 0;
-    for (; base + D <= nfull; base += D) {
+
+  u32x4 kf[KP], vf[2][DB];
+  auto read_k = [&](int slot) {
 #pragma unroll
-      for (int u = 0; u < D; ++u) step(std::false_type{}, u, base + u);
-    }
+    for (int x = 0; x < KP; ++x) kf[x] = ring[slot][x][lane];
+  };
+  // S^T = K Q^T (rows: keys, cols: queries) in two chains, one per part of
+  // q = q_hi + q_lo: a single chain of dependent MFMAs issues one every 52
+  // clocks instead of 32
+  struct Scores {
+    f32x16 hi, lo;
+  };
+  auto qk = [&](Scores& s) {
 #pragma unroll
-    for (int u = 0; u < D; ++u) {
-      const int i = base + u;
-      if (i < nfull) step(std::false_type{}, u, i);  // uniform
-      else if (i < nb) step(std::true_type{}, u, i);
+    for (int r = 0; r < 16; ++r) s.hi[r] = s.lo[r] = 0.f;
+#pragma unroll
+    for (int x = 0; x < KP; ++x) {
+      s.hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[x]), as_bf16x8(qf[0][x / 4][x % 4]), s.hi, 0, 0, 0);
+      s.lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[x]), as_bf16x8(qf[1][x / 4][x % 4]), s.lo, 0, 0, 0);
     }
-    wait_vmcnt_lds<0>();
-  } else if (nb > 0) {
-    // Q (loaded before the first DMAs) and block 0
+  };
+  // P as split bf16 (p_hi + p_lo), the operand of O^T += V^T P^T, of keys 8 t ..
+  // 8 t + 7 of the lane's 16, a part at a time: part u of n = 4 or 8 is a pair
+  // of keys or one plane of a pair
+  float p[16];
+  auto pack_part = [&](u32x4 (&pf)[2], int t, int u, int n) {
+    const int q = u * 4 / n;
+    const float x = p[8 * t + 2 * q], y = p[8 * t + 2 * q + 1];
+    if (n == 4 || u % 2 == 0) pf[0][q] = pack_bf16x2(x, y);
+    if (n == 4 || u % 2 == 1)
+      pf[1][q] = pack_bf16x2(x - __uint_as_float(pf[0][q] << 16), y - __uint_as_float(pf[0][q] & 0xffff0000u));
+  };
+  // One wave per SIMD: an MFMA leaves 28 of its 32 clocks to the wave's other
+  // instructions (measured: up to 6 vector instructions, or 4 and an exp2,
+  // between two MFMAs cost nothing, each further one 4 to 8 clocks), so step i
+  // is written as a sequence of MFMAs with their share of everything else:
+  // the score MFMAs of block i + 1 between the softmax of block i and its V
+  // reads, then, past the barrier, the P V MFMAs of block i between the second
+  // half of its packing, the K reads of block i + 2 and the DMA of block i + D.
+  // sched_barrier holds that order; left alone the compiler moves each LDS read
+  // next to its use and waits for it there.  The barrier (every wave's pieces of
+  // block i + 2 have landed, and every wave holds its V of block i) publishes
+  // slot i + 2 and frees slot i.  The split's last block, the only one that can be
+  // partial, is handled after the loop.  Issues past the last block re-read it
+  // into slots that are never consumed; every DMA has landed before the waves
+  // leave.
+  //
+  // What bounds it: at 8 x 16384 keys the matrix cores' power.  The step takes
+  // 1.48 kclk of 1.06 k (the MFMAs alone) but the shader clock falls to 1.6 GHz;
+  // 64 rows a wave, which halves the LDS reads and the DMA per MFMA, measured 3 %
+  // less.  Per launch, against two workgroups per CU with the reads beside their
+  // uses, on one box: 253 -> 244 us there, 69 -> 64 us at 1 x 30011 keys.
+  static_assert(D >= 3, "two blocks run ahead of the ring");
+  if (nb > 0) {
+    Scores sa, sb;
+    wait_vmcnt_lds<(D - 1) * PPW>();
+    __builtin_amdgcn_s_barrier();
+    read_k(0);
+    qk(sa);
+    {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, kb0 * 32 + 16 * hh + r < P ? sa.hi[r] + sa.lo[r] : -INFINITY);
+      m_ref = fmaxf(mx, __shfl_xor(mx, 32, 64)) * a.scale_log2;
+    }
     wait_vmcnt_lds<(D - 2) * PPW>();
     __builtin_amdgcn_s_barrier();
-    f32x16 sc = qk(0);
-    // block i (slot u = i % D) when block i + 1 exists
-    auto step = [&](auto tail, int u, int i) {
+    read_k(1);  // a single-block split reads a repeat of block 0 and leaves it
+    int slot = 0;  // i % D
+    auto step = [&](const Scores& s, Scores& sn, int i) {
+      u32x4 pf[2][2];
+      constexpr int S1 = 2 * KP, E = 16 / S1;  // score MFMAs; keys of the softmax per MFMA
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sn.hi[r] = sn.lo[r] = 0.f;
+#pragma unroll
+      for (int g = 0; g < S1; ++g) {
+        const int x = g >> 1;
+        f32x16& c = g & 1 ? sn.lo : sn.hi;
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[x]), as_bf16x8(qf[g & 1][x / 4][x % 4]), c, 0, 0, 0);
+        if (g < 2 * DB) vf[g / DB][g % DB] = ring[slot][KP + (g % DB) * 2 + g / DB][lane];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int r = g * E + e;
+          p[r] = __builtin_amdgcn_exp2f(fmaf(s.hi[r] + s.lo[r], a.scale_log2, -m_ref));
+          l_run += p[r];
+        }
+        if (g >= S1 / 2) pack_part(pf[0], 0, g - S1 / 2, S1 / 2);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       wait_vmcnt_lds<(D - 3) * PPW>();
       __builtin_amdgcn_s_barrier();
-      issue((u + D - 1) % D, kb0 + min(i + D - 1, nb - 1));
-      const f32x16 sn = qk((u + 1) % D);
-      // waves past the end of the head group compute a duplicate of the
-      // group's first head and write nothing
-      sv(tail, sc, u, kb0 + i, i == 0);
-      sc = sn;
+      const int s1 = slot + 1 == D ? 0 : slot + 1, s2 = s1 + 1 == D ? 0 : s1 + 1;
+      const int kb = kb0 + min(i + D, nb - 1);
+      constexpr int S2 = 4 * DB, HALF = 2 * DB;  // P V MFMAs
+      constexpr int PER = (PPW + S2 - KP - 1) / (S2 - KP);  // DMA pieces per MFMA behind the K reads
+#pragma unroll
+      for (int g = 0; g < S2; ++g) {
+        const int t = g / HALF, h = g / DB % 2, d = g % DB;
+        oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t][d]), as_bf16x8(pf[t][h]), oacc[d], 0, 0, 0);
+        if (g < KP) kf[g] = ring[s2][g][lane];
+        if (g < HALF) pack_part(pf[1], 1, g, HALF);
+        if (g >= KP) {
+#pragma unroll
+          for (int u = 0; u < PER; ++u)
+            if ((g - KP) * PER + u < PPW) issue_piece(slot, kb, (g - KP) * PER + u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      slot = s1;
     };
-    int base = 0;
-    for (; base + D < nb && base + D <= nfull; base += D) {
-#pragma unroll
-      for (int u = 0; u < D; ++u) step(std::false_type{}, u, base + u);
+    int i = 0;
+    for (; i + 2 < nb; i += 2) {
+      step(sa, sb, i);
+      step(sb, sa, i + 1);
     }
-    // the remaining blocks (at most D): full ones with a successor, then the
-    // last block (full or partial)
+    if (i + 1 < nb) {  // uniform
+      step(sa, sb, i);
+      sa = sb;
+      ++i;
+    }
+    // last block (i = nb - 1), full or partial: keys at or past P get
+    // probability 0, and their V (tree or stale values) is zeroed
 #pragma unroll
-    for (int u = 0; u < D; ++u) {
-      const int i = base + u;
-      if (i + 1 < nb) step(std::false_type{}, u, i);  // uniform; i + 1 < nb implies a full block
-      else if (i + 1 == nb) {
-        if (i < nfull) sv(std::false_type{}, sc, u, kb0 + i, i == 0);
-        else sv(std::true_type{}, sc, u, kb0 + i, i == 0);
+    for (int r = 0; r < 16; ++r) {
+      const float x = (kb0 + i) * 32 + 16 * hh + r < P ? sa.hi[r] + sa.lo[r] : -INFINITY;
+      p[r] = __builtin_amdgcn_exp2f(fmaf(x, a.scale_log2, -m_ref));
+      l_run += p[r];
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      u32x4 pf[2];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) pack_part(pf, t, u, 4);
+#pragma unroll
+      for (int d = 0; d < DB; ++d) {
+        u32x4 v = ring[slot][KP + d * 2 + t][lane];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // bf16 element 2q is the low half of dword q
+          const int key = (kb0 + i) * 32 + 16 * hh + 8 * t + 2 * q;
+          v[q] &= (key < P ? 0x0000ffffu : 0u) | (key + 1 < P ? 0xffff0000u : 0u);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v), as_bf16x8(pf[h]), oacc[d], 0, 0, 0);
       }
     }
     wait_vmcnt_lds<0>();
+    l_run += __shfl_xor(l_run, 32, 64);
   }
   // a row whose probabilities went past the cap marks its partial invalid
   // (l < 0); the merge recomputes that split exactly
@@ -359,9 +338,7 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(A
   constexpr int RPI = 64 / CHUNKS;  // rows per wave-wide store
   static_assert(NW * 32 * DH * 4 <= (int)sizeof(ring), "transpose tiles fit in the ring");
   __builtin_amdgcn_s_barrier();
-  if (!head_live) return;
-  float* po = a.part_o + ((((long long)b * a.Hq + hq) * a.sp + split) * qrows + qb * 32) * DH;
-  float* pml = a.part_ml + ((((long long)b * a.Hq + hq) * a.sp + split) * qrows + qb * 32) * 2;
+  if (!tile_live) return;
   float* tile = reinterpret_cast<float*>(&ring[0][0][0]) + w * 32 * DH;
 #pragma unroll
   for (int d = 0; d < DB; ++d)
@@ -372,61 +349,65 @@ __global__ __launch_bounds__(64 * NW, LEAN ? 2 : 1) void tree_attention_kernel(A
           make_float4(oacc[d][4 * rg], oacc[d][4 * rg + 1], oacc[d][4 * rg + 2], oacc[d][4 * rg + 3]);
     }
   // rows of absent nodes are not stored (the merge reads live rows only)
-  const int live_rows = min(32, n_nodes - qb * 32);
+  const long long head0 = (long long)b * a.Hq + hk * G;
+  auto part_row = [&](int r, int s) { return ((head0 + row_head(r)) * a.sp + s) * qrows + row_node(r); };
+  auto row_live = [&](int r) { return row_node(r) < n_nodes && row_head(r) < G; };
 #pragma unroll
   for (int n = 0; n < 32 / RPI; ++n) {
-    if (n * RPI >= live_rows) break;  // uniform
     const int r = n * RPI + lane / CHUNKS, c = lane % CHUNKS;
-    *reinterpret_cast<float4*>(po + r * DH + 4 * c) =
-        *reinterpret_cast<const float4*>(tile + r * DH + 4 * (c ^ (r & 7)));
+    if (row_live(r))
+      *reinterpret_cast<float4*>(a.part_o + part_row(r, split) * DH + 4 * c) =
+          *reinterpret_cast<const float4*>(tile + r * DH + 4 * (c ^ (r & 7)));
   }
-  if (hh == 0 && col < live_rows) {
-    pml[2 * col] = m_ref;
-    pml[2 * col + 1] = l_run;
+  if (hh == 0 && row_live(col)) {
+    float* pml = a.part_ml + part_row(col, split) * 2;
+    pml[0] = m_ref;
+    pml[1] = l_run;
     // the sequence's last split marks its unused slots empty, so that the
     // merge reads all sp slots without knowing the split count
     if (RAGGED && split == nsplit - 1)
       for (int s2 = nsplit; s2 < a.sp; ++s2) {
-        float* pe = a.part_ml + ((((long long)b * a.Hq + hq) * a.sp + s2) * qrows + qb * 32 + col) * 2;
+        float* pe = a.part_ml + part_row(col, s2) * 2;
         pe[0] = -INFINITY;
         pe[1] = 0.f;
       }
   }
 }
 
-int attn_waves(int group) { return group >= 4 ? 4 : group >= 2 ? 2 : 1; }
+AttnShape attn_shape(int group, int max_tree) {
+  AttnShape s;
+  s.qblocks = (max_tree + 31) / 32;
+  // a group's rows packed into one tile: the vector work and the MFMAs of a
+  // short chain are those of one row tile instead of one per head
+  s.pack = group * max_tree <= 32;
+  s.tiles = s.pack ? 1 : group * s.qblocks;
+  s.nw = s.tiles >= 4 ? 4 : s.tiles >= 2 ? 2 : 1;
+  s.per_unit = (s.tiles + s.nw - 1) / s.nw;
+  return s;
+}
 
-template <int DH, int NW>
+template <int DH, int NW, bool PACK>
 static void launch_attn_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
-  // two workgroups per CU pay off once the grid fills them (measured at 8
-  // sequences x 16384 keys); smaller grids keep the one-wave-per-SIMD form
-  const bool lean = grid.x >= 512;
-  if (a.meta.split_tab) {
-    if (lean) hipLaunchKernelGGL((tree_attention_kernel<DH, NW, true, true>), grid, dim3(64 * NW), 0, s, a);
-    else hipLaunchKernelGGL((tree_attention_kernel<DH, NW, true, false>), grid, dim3(64 * NW), 0, s, a);
-  } else {
-    if (lean) hipLaunchKernelGGL((tree_attention_kernel<DH, NW, false, true>), grid, dim3(64 * NW), 0, s, a);
-    else hipLaunchKernelGGL((tree_attention_kernel<DH, NW, false, false>), grid, dim3(64 * NW), 0, s, a);
-  }
+  if (a.meta.split_tab) hipLaunchKernelGGL((tree_attention_kernel<DH, NW, true, PACK>), grid, dim3(64 * NW), 0, s, a);
+  else hipLaunchKernelGGL((tree_attention_kernel<DH, NW, false, PACK>), grid, dim3(64 * NW), 0, s, a);
 }
 
 template <int DH>
-static void launch_attn_dh(const AttnArgs& a, int nw, dim3 grid, hipStream_t s) {
-  if (nw == 4) launch_attn_nw<DH, 4>(a, grid, s);
-  else if (nw == 2) launch_attn_nw<DH, 2>(a, grid, s);
-  else launch_attn_nw<DH, 1>(a, grid, s);
+static void launch_attn_dh(const AttnArgs& a, const AttnShape& sh, dim3 grid, hipStream_t s) {
+  if (sh.pack) launch_attn_nw<DH, 1, true>(a, grid, s);
+  else if (sh.nw == 4) launch_attn_nw<DH, 4, false>(a, grid, s);
+  else if (sh.nw == 2) launch_attn_nw<DH, 2, false>(a, grid, s);
+  else launch_attn_nw<DH, 1, false>(a, grid, s);
 }
 
 hipError_t launch_attention(const AttnArgs& a, int batch, hipStream_t s) {
   if (a.batch != batch) return hipErrorInvalidValue;
-  const int G = a.Hq / a.Hkv;
-  const int nw = attn_waves(G);
-  if (a.units < 1 || a.sp < 1 || a.sp > 16) return hipErrorInvalidValue;
+  const AttnShape sh = attn_shape(a.Hq / a.Hkv, a.max_tree);
+  if (a.units < 1 || a.sp < 1 || a.sp > 16 || a.qblocks != sh.qblocks) return hipErrorInvalidValue;
   const int streams = a.units * a.Hkv;
-  const int per_unit = ((G + nw - 1) / nw) * a.qblocks;
-  dim3 grid(((streams + 7) / 8) * 8 * per_unit);
-  if (a.dh == 128) launch_attn_dh<128>(a, nw, grid, s);
-  else if (a.dh == 64) launch_attn_dh<64>(a, nw, grid, s);
+  dim3 grid(((streams + 7) / 8) * 8 * sh.per_unit);
+  if (a.dh == 128) launch_attn_dh<128>(a, sh, grid, s);
+  else if (a.dh == 64) launch_attn_dh<64>(a, sh, grid, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -184,7 +184,14 @@ hipError_t launch_qkv_rope(const float* qkv_parts, int n_parts, long long part_s
                            hipStream_t s);
 hipError_t launch_attention(const AttnArgs& a, int batch, hipStream_t s);
 constexpr int ATTN_RING = 4;  // 32-key K/V blocks in flight per attention workgroup
-int attn_waves(int group);    // waves (query heads) per attention workgroup
+// How an attention launch cuts the rows of one (sequence, KV head): `tiles` row
+// tiles of 32 (one query head's, or all heads' packed), nw of them (one wave
+// each) per workgroup, per_unit workgroups.
+struct AttnShape {
+  int qblocks, tiles, nw, per_unit;
+  bool pack;
+};
+AttnShape attn_shape(int group, int max_tree);
 hipError_t launch_attn_combine(const float* part_o, const float* part_ml, StepMeta meta, int Hq, int Hkv, int dh,
                                int slots, int sp, int qrows, int max_tree, int batch, const uint16_t* q,
                                const uint16_t* q_lo, TreeKV32 tree, PrefixKV prefix, float scale_log2,

@@ -782,14 +782,15 @@ int griffin_verify_init(const griffin_model_desc* desc, const griffin_weights* w
   c->attn_w = d.n_q_heads * d.head_dim;
   c->qblocks = cdiv(d.max_tree, 32);
   {
-    // key splits: about 512 attention workgroups, at least two 32-key
-    // blocks per split and at most 16 splits.  A grid of 512 or more runs
-    // the kernel's two-workgroups-per-CU form; smaller ones (a single
-    // sequence: 16 splits x 16 units) hold one wave per SIMD
-    const int G = d.n_q_heads / d.n_kv_heads, nw = attn_waves(G);
-    const int units = d.max_batch * d.n_kv_heads * cdiv(G, nw) * c->qblocks;
-    const int by_par = cdiv(512, units);
-    const int by_len = std::max(1, d.kv_capacity / 64);
+    // key splits: a workgroup on every CU with four waves of it, two on
+    // every CU with fewer (the ring's LDS holds two), at least four 32-key
+    // blocks per split at full capacity (with two, a 1024-key Llama-2-7B step
+    // paid 1.6 us more in the merge and 0.4 in the attention) and at most 16
+    // splits
+    const AttnShape sh = attn_shape(d.n_q_heads / d.n_kv_heads, d.max_tree);
+    const int units = d.max_batch * d.n_kv_heads * sh.per_unit;
+    const int by_par = cdiv(sh.nw == 4 ? 256 : 512, units);
+    const int by_len = std::max(1, d.kv_capacity / 128);
     c->attn_splits = std::max(1, std::min(std::min(by_len, by_par), 16));
     // With several sequences a step has batch * attn_splits split units,
     // dealt to its sequences in proportion to their prefix lengths (a split
