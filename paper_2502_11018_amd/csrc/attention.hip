@@ -432,8 +432,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
                                                            const uint16_t* __restrict__ q,
                                                            const uint16_t* __restrict__ q_lo, TreeKV32 tree,
                                                            PrefixKV prefix, float scale_log2,
-                                                           uint16_t* __restrict__ o_out, int o_ks) {
-  const int r = blockIdx.x;
+                                                           uint16_t* __restrict__ o_out, int o_ks, int row0) {
+  const int r = row0 + blockIdx.x;
   const int b = r / max_tree, i = r % max_tree;
   const int quads = dh / 4;
   const int t = blockIdx.y * blockDim.x + threadIdx.x;
@@ -574,22 +574,22 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 }
 
 hipError_t launch_attn_combine(const float* part_o, const float* part_ml, StepMeta meta, int Hq, int Hkv, int dh,
-                               int slots, int sp, int qrows, int max_tree, int batch, const uint16_t* q,
+                               int slots, int sp, int qrows, int max_tree, int row0, int rows, const uint16_t* q,
                                const uint16_t* q_lo, TreeKV32 tree, PrefixKV prefix, float scale_log2,
                                uint16_t* o_out, int o_ks, hipStream_t s) {
   const int quads = dh / 4;
   if (256 % quads != 0 || slots < 1 || slots > sp) return hipErrorInvalidValue;
   const int items = Hq * quads;
-  const dim3 grid(batch * max_tree, (items + 255) / 256);
+  const dim3 grid(rows, (items + 255) / 256);
   switch (slots) {
 #define GRIFFIN_COMB_CASE(n)                                                                                   \
   case n:                                                                                                     \
     if (meta.split_tab)                                                                                       \
       hipLaunchKernelGGL((attn_combine_kernel<n, true>), grid, dim3(256), 0, s, part_o, part_ml, meta, Hq, Hkv,   \
-                         dh, sp, qrows, max_tree, q, q_lo, tree, prefix, scale_log2, o_out, o_ks);                \
+                         dh, sp, qrows, max_tree, q, q_lo, tree, prefix, scale_log2, o_out, o_ks, row0);          \
     else                                                                                                      \
       hipLaunchKernelGGL((attn_combine_kernel<n, false>), grid, dim3(256), 0, s, part_o, part_ml, meta, Hq, Hkv,  \
-                         dh, sp, qrows, max_tree, q, q_lo, tree, prefix, scale_log2, o_out, o_ks);                \
+                         dh, sp, qrows, max_tree, q, q_lo, tree, prefix, scale_log2, o_out, o_ks, row0);          \
     break;
     GRIFFIN_COMB_CASE(1) GRIFFIN_COMB_CASE(2) GRIFFIN_COMB_CASE(3) GRIFFIN_COMB_CASE(4) GRIFFIN_COMB_CASE(5)
     GRIFFIN_COMB_CASE(6) GRIFFIN_COMB_CASE(7) GRIFFIN_COMB_CASE(8) GRIFFIN_COMB_CASE(9) GRIFFIN_COMB_CASE(10)

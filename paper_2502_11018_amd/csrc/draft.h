@@ -11,7 +11,8 @@ namespace griffin {
 
 struct DraftArgs {
   int d, tgf_dim;            // model width, TGF expansion width
-  int rows, mpad, max_tree;  // row slots of the step (batch * max_tree), padded to 64
+  int rows, max_tree;        // row slots of the step (batch * max_tree)
+  int row0, nr;              // rows the pass works on: [row0, row0 + nr), padding included
   float ln_eps, rms_eps;
   const uint16_t* embed;     // target's embedding [V][d] (bf16)
   const float* root_feat;    // [batch][d] input feature of each root
@@ -34,11 +35,11 @@ hipError_t launch_draft_front(const DraftArgs& a, const StepMeta& meta, int stag
 // TEH, stage 0: y = x + layer residual -> x_h; 1: F^R -> feat_r, RMSNorm(F^P) -> xn.
 hipError_t launch_draft_head(const DraftArgs& a, const StepMeta& meta, const ResidualAdd& add, int stage,
                              hipStream_t s);
-// Top-k (k <= 16) tokens and log-probabilities of every live row of logits
-// [rows][ld] (V <= 524288); `work` holds draft_topk_work_bytes(rows, V).
+// Top-k (k <= 16) tokens and log-probabilities of the live nodes [first,
+// first + count) of every tree, from logits [rows][ld] (V <= 524288); `work` holds draft_topk_work_bytes(rows, V).
 size_t draft_topk_work_bytes(int rows, int V);
 hipError_t launch_draft_topk(const float* logits, long long ld, int V, const StepMeta& meta, int rows, int max_tree,
-                             int k, int32_t* tok, float* logp, float* work, hipStream_t s);
+                             int first, int count, int k, int32_t* tok, float* logp, float* work, hipStream_t s);
 
 }  // namespace griffin
 

@@ -43,7 +43,7 @@ __device__ __forceinline__ float dblock_sum(float v, float* red) { return block_
 
 // [F, e] of every row as the operand of W_m (K = 2d).
 __global__ __launch_bounds__(DT) void draft_in_kernel(DraftArgs a, StepMeta meta) {  // grid (rows, y)
-  const int r = blockIdx.x, d = a.d;
+  const int r = a.row0 + blockIdx.x, d = a.d;
   const bool live = draft_live(meta, r, a.rows, a.max_tree);
   const int b = r / a.max_tree, i = r % a.max_tree;
   const float* f = a.node_feat ? a.node_feat + (long long)min(r, a.rows - 1) * d
@@ -102,7 +102,7 @@ __device__ __forceinline__ float2 block_sum2(float x, float y, float* red /* >= 
 // operand of W_u (K = 2d).
 __global__ __launch_bounds__(DR) void draft_fuse_kernel(DraftArgs a, StepMeta meta) {
   __shared__ float red[32];
-  const int r = blockIdx.x, d = a.d;
+  const int r = a.row0 + blockIdx.x, d = a.d;
   const bool live = draft_live(meta, r, a.rows, a.max_tree);
   const uint16_t* e = a.embed + (long long)meta.token[min(r, a.rows - 1)] * d;
   float hv[RV], ev[RV];
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(DR) void draft_fuse_kernel(DraftArgs a, StepMeta me
 
 // SiLU(sum of the W_u partials + b_u) as the operand of W_d (K = tgf_dim).
 __global__ __launch_bounds__(DT) void draft_silu_kernel(DraftArgs a, StepMeta meta) {
-  const int r = blockIdx.x, e = a.tgf_dim;
+  const int r = a.row0 + blockIdx.x, e = a.tgf_dim;
   const bool live = draft_live(meta, r, a.rows, a.max_tree);
   for (int k = blockIdx.y * DT + threadIdx.x; k < e; k += gridDim.y * DT) {
     float v = 0.f;
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(DT) void draft_silu_kernel(DraftArgs a, StepMeta me
 
 // o = sum of the W_d partials + b_d + h: the decoder layer's input x.
 __global__ __launch_bounds__(DT) void draft_out_kernel(DraftArgs a, StepMeta meta) {
-  const int r = blockIdx.x, d = a.d;
+  const int r = a.row0 + blockIdx.x, d = a.d;
   const bool live = draft_live(meta, r, a.rows, a.max_tree);
   for (int k = blockIdx.y * DT + threadIdx.x; k < d; k += gridDim.y * DT) {
     const long long at = (long long)r * d + k;
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(DT) void draft_out_kernel(DraftArgs a, StepMeta met
 // y = x + the decoder layer's last residual (down-projection partials), as
 // the operand of [W_p; W_r] (K = d).
 __global__ __launch_bounds__(DT) void draft_head_in_kernel(DraftArgs a, StepMeta meta, ResidualAdd add) {
-  const int r = blockIdx.x, d = a.d;
+  const int r = a.row0 + blockIdx.x, d = a.d;
   const bool live = draft_live(meta, r, a.rows, a.max_tree);
   for (int k = blockIdx.y * DT + threadIdx.x; k < d; k += gridDim.y * DT) {
     const long long at = (long long)r * d + k;
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(DT) void draft_head_in_kernel(DraftArgs a, StepMeta
 // RMSNorm(F^P) times the final norm's gain becomes the LM head's operand.
 __global__ __launch_bounds__(DR) void draft_head_out_kernel(DraftArgs a, StepMeta meta) {
   __shared__ float red[32];
-  const int r = blockIdx.x, d = a.d;
+  const int r = a.row0 + blockIdx.x, d = a.d;
   const bool live = draft_live(meta, r, a.rows, a.max_tree);
   float pv[RV], qv[RV];
 #pragma unroll
@@ -240,10 +240,11 @@ __host__ __device__ __forceinline__ int topk_slice_len(int V) {
 
 template <bool VEC>
 __global__ __launch_bounds__(TS) void draft_topk_slice_kernel(const float* logits, long long ld, int V, StepMeta meta,
-                                                             int rows, int max_tree, int k, float* part) {
+                                                             int rows, int max_tree, int first, int count, int k,
+                                                             float* part) {
   __shared__ float wv[2][TS / 64], red[16];
   __shared__ int wi[2][TS / 64];
-  const int r = blockIdx.x, slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = (int)blockIdx.x / count * max_tree + first + (int)blockIdx.x % count, slice = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (!draft_live(meta, r, rows, max_tree)) return;  // uniform
   const int len = topk_slice_len(V), lo = slice * len, hi = min(V, lo + len);
   const float* lg = logits + (long long)r * ld;
@@ -347,10 +348,11 @@ __global__ __launch_bounds__(TS) void draft_topk_slice_kernel(const float* logit
 }
 
 __global__ __launch_bounds__(64) void draft_topk_merge_kernel(const float* part, int nslice, StepMeta meta, int rows,
-                                                             int max_tree, int k, int32_t* tok_out, float* logp_out) {
+                                                             int max_tree, int first, int count, int k,
+                                                             int32_t* tok_out, float* logp_out) {
   __shared__ float cv[MAX_SLICES * DK];
   __shared__ int ci[MAX_SLICES * DK];
-  const int r = blockIdx.x, lane = threadIdx.x;
+  const int r = (int)blockIdx.x / count * max_tree + first + (int)blockIdx.x % count, lane = threadIdx.x;
   if (!draft_live(meta, r, rows, max_tree)) return;  // uniform
   const float* pr = part + (long long)r * nslice * PART_WORDS;
   const float Ms = lane < nslice ? pr[lane * PART_WORDS + 2 * DK] : -INFINITY;
@@ -385,12 +387,12 @@ __global__ __launch_bounds__(64) void draft_topk_merge_kernel(const float* part,
 }
 
 hipError_t launch_draft_front(const DraftArgs& a, const StepMeta& meta, int stage, hipStream_t s) {
-  const dim3 g(a.mpad);
+  const dim3 g(a.nr);
   switch (stage) {
-    case 0: hipLaunchKernelGGL(draft_in_kernel, dim3(a.mpad, 8), dim3(DT), 0, s, a, meta); break;
+    case 0: hipLaunchKernelGGL(draft_in_kernel, dim3(a.nr, 8), dim3(DT), 0, s, a, meta); break;
     case 1: hipLaunchKernelGGL(draft_fuse_kernel, g, dim3(DR), 0, s, a, meta); break;
-    case 2: hipLaunchKernelGGL(draft_silu_kernel, dim3(a.mpad, 16), dim3(DT), 0, s, a, meta); break;
-    case 3: hipLaunchKernelGGL(draft_out_kernel, dim3(a.mpad, 8), dim3(DT), 0, s, a, meta); break;
+    case 2: hipLaunchKernelGGL(draft_silu_kernel, dim3(a.nr, 16), dim3(DT), 0, s, a, meta); break;
+    case 3: hipLaunchKernelGGL(draft_out_kernel, dim3(a.nr, 8), dim3(DT), 0, s, a, meta); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -400,9 +402,9 @@ hipError_t launch_draft_head(const DraftArgs& a, const StepMeta& meta, const Res
                              hipStream_t s) {
   if (add.slot != nullptr) return hipErrorInvalidValue;  // dense decoder layer only
   if (stage == 0)
-    hipLaunchKernelGGL(draft_head_in_kernel, dim3(a.mpad, 8), dim3(DT), 0, s, a, meta, add);
+    hipLaunchKernelGGL(draft_head_in_kernel, dim3(a.nr, 8), dim3(DT), 0, s, a, meta, add);
   else
-    hipLaunchKernelGGL(draft_head_out_kernel, dim3(a.mpad), dim3(DR), 0, s, a, meta);
+    hipLaunchKernelGGL(draft_head_out_kernel, dim3(a.nr), dim3(DR), 0, s, a, meta);
   return hipGetLastError();
 }
 
@@ -411,17 +413,18 @@ size_t draft_topk_work_bytes(int rows, int V) {
 }
 
 hipError_t launch_draft_topk(const float* logits, long long ld, int V, const StepMeta& meta, int rows, int max_tree,
-                             int k, int32_t* tok, float* logp, float* work, hipStream_t s) {
-  if (k < 1 || k > DK || V < k || topk_slices(V) > MAX_SLICES) return hipErrorInvalidValue;
+                             int first, int count, int k, int32_t* tok, float* logp, float* work, hipStream_t s) {
+  if (first < 0 || count < 1 || first + count > max_tree || k < 1 || k > DK || V < k || topk_slices(V) > MAX_SLICES) return hipErrorInvalidValue;
   const int ns = topk_slices(V);
+  const int n = rows / max_tree * count;
   if ((V & 3) == 0 && (ld & 3) == 0)  // 16-byte aligned rows and slices
-    hipLaunchKernelGGL(draft_topk_slice_kernel<true>, dim3(rows, ns), dim3(TS), 0, s, logits, ld, V, meta, rows,
-                       max_tree, k, work);
+    hipLaunchKernelGGL(draft_topk_slice_kernel<true>, dim3(n, ns), dim3(TS), 0, s, logits, ld, V, meta, rows,
+                       max_tree, first, count, k, work);
   else
-    hipLaunchKernelGGL(draft_topk_slice_kernel<false>, dim3(rows, ns), dim3(TS), 0, s, logits, ld, V, meta, rows,
-                       max_tree, k, work);
-  hipLaunchKernelGGL(draft_topk_merge_kernel, dim3(rows), dim3(64), 0, s, work, ns, meta, rows, max_tree, k, tok,
-                     logp);
+    hipLaunchKernelGGL(draft_topk_slice_kernel<false>, dim3(n, ns), dim3(TS), 0, s, logits, ld, V, meta, rows,
+                       max_tree, first, count, k, work);
+  hipLaunchKernelGGL(draft_topk_merge_kernel, dim3(n), dim3(64), 0, s, work, ns, meta, rows, max_tree, first, count, k,
+                     tok, logp);
   return hipGetLastError();
 }
 

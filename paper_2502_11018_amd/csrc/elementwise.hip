@@ -201,10 +201,10 @@ __global__ __launch_bounds__(RN_THREADS) void residual_rmsnorm_kernel(float* __r
                                                                       const uint16_t* __restrict__ gain,
                                                                       float eps, int d,
                                                                       uint16_t* __restrict__ xn, int xn_ks,
-                                                                      Router rt) {
+                                                                      Router rt, int row0) {
   __shared__ float red[16];
-  const int r = blockIdx.x;
-  if (rt.clear && r == 0 && threadIdx.x < rt.n_clear) rt.clear[threadIdx.x] = 0;
+  const int r = row0 + blockIdx.x;
+  if (rt.clear && blockIdx.x == 0 && threadIdx.x < rt.n_clear) rt.clear[threadIdx.x] = 0;
   float* __restrict__ xr = x + (long long)r * d;
   const float* __restrict__ parts = add.parts;
   const int groups = d >> 2;
@@ -289,11 +289,11 @@ __global__ __launch_bounds__(RN_THREADS) void residual_rmsnorm_kernel(float* __r
 
 template <int NP>
 static hipError_t launch_rn(float* x, const ResidualAdd& add, const uint16_t* gain, float eps, int rows, int d,
-                            uint16_t* xn, int xn_ks, hipStream_t s, const Router& rt) {
+                            uint16_t* xn, int xn_ks, hipStream_t s, const Router& rt, int row0) {
   const int gpt = (d / 4 + RN_THREADS - 1) / RN_THREADS;  // float4 groups per thread
 #define GRIFFIN_RN_LAUNCH(G)                                                                                    \
   hipLaunchKernelGGL((residual_rmsnorm_kernel<NP, G>), dim3(rows), dim3(RN_THREADS), 0, s, x, add, gain, eps, d, \
-                     xn, xn_ks, rt)
+                     xn, xn_ks, rt, row0)
   if (gpt <= 1) GRIFFIN_RN_LAUNCH(1);
   else if (gpt <= 2) GRIFFIN_RN_LAUNCH(2);
   else if (gpt <= 4) GRIFFIN_RN_LAUNCH(4);
@@ -303,17 +303,17 @@ static hipError_t launch_rn(float* x, const ResidualAdd& add, const uint16_t* ga
 }
 
 hipError_t launch_residual_rmsnorm(float* x, const ResidualAdd& add, const uint16_t* gain, float eps, int rows,
-                                   int d, uint16_t* xn, int xn_ks, hipStream_t s, const Router& rt) {
+                                   int d, uint16_t* xn, int xn_ks, hipStream_t s, const Router& rt, int row0) {
   if (d % 4 != 0 || d > 32 * RN_THREADS || d > 32768 || add.n_parts > RN_SPLITS) return hipErrorInvalidValue;
   if (rt.w && (rt.n_experts < 1 || rt.n_experts > 64 || rt.top_k < 1 || rt.top_k > 4)) return hipErrorInvalidValue;
   if (rt.count && (!rt.w || !rt.slot || !rt.xe || rt.padded_rows < rows || rt.cap < rt.padded_rows))
     return hipErrorInvalidValue;
   if (rt.clear && (rt.n_clear < 0 || rt.n_clear > RN_THREADS)) return hipErrorInvalidValue;
-  if (add.parts == nullptr) return launch_rn<0>(x, add, gain, eps, rows, d, xn, xn_ks, s, rt);
-  if (add.slot != nullptr) return launch_rn<-1>(x, add, gain, eps, rows, d, xn, xn_ks, s, rt);
+  if (add.parts == nullptr) return launch_rn<0>(x, add, gain, eps, rows, d, xn, xn_ks, s, rt, row0);
+  if (add.slot != nullptr) return launch_rn<-1>(x, add, gain, eps, rows, d, xn, xn_ks, s, rt, row0);
   switch (add.n_parts) {
 #define GRIFFIN_RN_CASE(n) \
-  case n: return launch_rn<n>(x, add, gain, eps, rows, d, xn, xn_ks, s, rt);
+  case n: return launch_rn<n>(x, add, gain, eps, rows, d, xn, xn_ks, s, rt, row0);
     GRIFFIN_RN_CASE(1) GRIFFIN_RN_CASE(2) GRIFFIN_RN_CASE(3) GRIFFIN_RN_CASE(4) GRIFFIN_RN_CASE(5)
     GRIFFIN_RN_CASE(6) GRIFFIN_RN_CASE(7) GRIFFIN_RN_CASE(8) GRIFFIN_RN_CASE(9) GRIFFIN_RN_CASE(10)
     GRIFFIN_RN_CASE(11) GRIFFIN_RN_CASE(12) GRIFFIN_RN_CASE(13) GRIFFIN_RN_CASE(14) GRIFFIN_RN_CASE(15)
@@ -340,8 +340,8 @@ __global__ __launch_bounds__(256) void qkv_rope_kernel(const float* __restrict__
                                                        int Hq, int Hkv, int dh, int max_tree, int kv_cap,
                                                        uint16_t* __restrict__ q_out, uint16_t* __restrict__ q_lo,
                                                        uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
-                                                       TreeKV32 tree) {
-  const int r = blockIdx.x;
+                                                       TreeKV32 tree, int row0) {
+  const int r = row0 + blockIdx.x;
   const int b = r / max_tree, i = r % max_tree;
   const int half = dh >> 1;
   const int heads = Hq + 2 * Hkv;
@@ -404,16 +404,16 @@ __global__ __launch_bounds__(256) void qkv_rope_kernel(const float* __restrict__
 }
 
 hipError_t launch_qkv_rope(const float* qkv_parts, int n_parts, long long part_stride, StepMeta meta,
-                           const double* inv_freq, int Hq, int Hkv, int dh, int max_tree, int batch, int kv_cap,
+                           const double* inv_freq, int Hq, int Hkv, int dh, int max_tree, int row0, int rows, int kv_cap,
                            uint16_t* q_out, uint16_t* q_lo, uint16_t* k_cache_l, uint16_t* v_cache_l, TreeKV32 tree,
                            hipStream_t s) {
   const int items = (Hq + 2 * Hkv) * (dh / 2);
-  const dim3 grid(batch * max_tree, (items + 255) / 256);
+  const dim3 grid(rows, (items + 255) / 256);
   switch (n_parts) {
 #define GRIFFIN_ROPE_CASE(n)                                                                                     \
   case n:                                                                                                       \
     hipLaunchKernelGGL(qkv_rope_kernel<n>, grid, dim3(256), 0, s, qkv_parts, part_stride, meta, inv_freq, Hq,     \
-                       Hkv, dh, max_tree, kv_cap, q_out, q_lo, k_cache_l, v_cache_l, tree);                     \
+                       Hkv, dh, max_tree, kv_cap, q_out, q_lo, k_cache_l, v_cache_l, tree, row0);               \
     break;
     GRIFFIN_ROPE_CASE(1) GRIFFIN_ROPE_CASE(2) GRIFFIN_ROPE_CASE(3) GRIFFIN_ROPE_CASE(4) GRIFFIN_ROPE_CASE(5)
     GRIFFIN_ROPE_CASE(6) GRIFFIN_ROPE_CASE(7) GRIFFIN_ROPE_CASE(8) GRIFFIN_ROPE_CASE(9) GRIFFIN_ROPE_CASE(10)

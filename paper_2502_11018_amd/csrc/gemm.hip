@@ -33,51 +33,53 @@
 
 namespace griffin {
 
-template <int EPI, int NB, int WN, int PF, int KS, bool XLO, bool NT_W>
-__global__ __launch_bounds__(64 * WN * KS) void gemm_kernel(GemmArgs a) {
-  // per step: {hi, lo} (XLO) or {hi} x {rows 0-31, 32-63} x 4 pieces of 1 KB
+// Half tiles: a step with at most 32 live rows (short chains, small trees, a
+// draft's frontier, plain decoding) or an expert that was routed no more
+// stages and multiplies one 32-row half.  The activation pieces come through
+// the same L1 queue as the weights, byte for byte as many of them in a full
+// tile, so halving them is worth more than the MFMAs they feed: Mixtral-8x7B
+// shape, 61 rows over 8 experts, 4 layers: step 2516 -> 2392 us; a draft's
+// catch-up on 5 tokens 98.8 -> 88.4 us, its 60-token tree (with only the new
+// nodes' half per pass) 3398 -> 3073 us.  An expert's count is only known on
+// the device, so its kernel holds both forms and picks by the count.
+
+// LDS bytes of the activation ring: per slot and slice {hi, lo} (XLO) or {hi}
+// x MB row halves x 4 pieces of 1 KB.
+template <int PF, int KS, bool XLO, int MB>
+constexpr int kRingPieces = PF * KS * 4 * MB * (XLO ? 2 : 1);
+
+// One workgroup's part of the product for MB 32-row halves from half mb0 of
+// row tile m_tile.
+template <int EPI, int NB, int WN, int PF, int KS, bool XLO, bool NT_W, int MB>
+__device__ __forceinline__ void gemm_body(const GemmArgs& a, u32x4* ring, int e, int m_tile, int mb0, int wg,
+                                          int rows_e) {
   constexpr int XH = XLO ? 2 : 1;
-  constexpr int XPIECES = 8 * XH;
+  constexpr int XPIECES = 4 * MB * XH;
   constexpr int XP = XPIECES / WN;          // activation pieces each wave stages per step
   constexpr int LOADS = NB * 4 + XP;        // vector-memory instructions per stage per wave
   static_assert(LOADS * (PF - 2) < 64, "wait count out of range");
   static_assert(PF >= 2 && XPIECES % WN == 0, "pipeline shape");
-  static_assert(WN * NB * 8 <= PF * KS * XPIECES || KS == 1, "K-split merge buffer");
-  __shared__ u32x4 xs[PF][KS][XPIECES][64];
+  static_assert(WN * NB * 4 * MB <= PF * KS * XPIECES || KS == 1, "K-split merge buffer");
+  u32x4(&xs)[PF][KS][XPIECES][64] = *reinterpret_cast<u32x4(*)[PF][KS][XPIECES][64]>(ring);
 
-  stamp_begin(a.stamp);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wc = wave % WN;            // column group of this wave
   const int kh = wave / WN;            // K slice of this wave inside the workgroup
-  const int e = blockIdx.y;
-  // XCD-aware decode: workgroups are dispatched round-robin over the 8 XCDs
-  // (linear id % 8, and the grid's x extent is a multiple of 8), so the
-  // workgroups of the row tiles that stream the same weights get the same
-  // id % 8 and the re-reads of those weights hit that XCD's L2.
-  int m_tile = 0, wg = blockIdx.x;
-  if (a.m_tiles > 1) {
-    const int grp = blockIdx.x / (8 * a.m_tiles), r = blockIdx.x % (8 * a.m_tiles);
-    m_tile = r >> 3;
-    wg = grp * 8 + (r & 7);
-    if (wg >= a.n_wgs) return;  // padding of the grid to a multiple of 8 (uniform)
-  }
   const int zsplit = blockIdx.z;       // output split (its KS slices are merged in the workgroup)
   const int split = zsplit * KS + kh;  // K slice of this wave's weight stream
-  const int rows_e = a.count ? a.count[e] : a.m_tiles * 64;
-  if (m_tile * 64 >= rows_e) return;   // uniform over the workgroup
 
   const long long Q = (long long)a.n_wgs * a.splits * WN;
   const long long q = ((long long)split * a.n_wgs + wg) * WN + wc;
   const uint16_t* W = a.W + (long long)e * a.w_estride + q * NB * 2048 + lane * 8;
   const long long wstep = Q * NB * 2048;  // elements between consecutive steps of a stream
   const uint16_t* X = a.X + ((long long)(e * a.x_etiles + m_tile) * a.x_ks + (long long)zsplit * KS * a.len) * XPACK_STEP +
-                      lane * 8;
+                      mb0 * 2048 + lane * 8;
 
-  f32x16 acc[NB][2];
+  f32x16 acc[NB][MB];
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[b][mb][i] = 0.f;
 
@@ -102,20 +104,21 @@ __global__ __launch_bounds__(64 * WN * KS) void gemm_kernel(GemmArgs a) {
 #pragma unroll
     for (int p = 0; p < XP; ++p) {
       const int pp = wave * XP + p, sk = pp / XPIECES, pc = pp % XPIECES;  // slice, piece
-      __builtin_amdgcn_global_load_lds((const void*)(X + ((long long)sk * a.len + t) * XPACK_STEP + pc * 512),
+      const int src = pc / (4 * MB) * XPACK_LO + pc % (4 * MB) * 512;       // plane, half and piece in the packed step
+      __builtin_amdgcn_global_load_lds((const void*)(X + ((long long)sk * a.len + t) * XPACK_STEP + src),
                                        (lds_void*)&xs[slot][sk][pc][0], 16, 0, 0);
     }
   };
   // Consume stage t from slot u: the weights times the activation's bf16 high
   // part plus, with XLO, its bf16 low part (two MFMAs into one accumulator).
   auto compute = [&](int u) {
-    u32x4 xv[XH][2][4];
+    u32x4 xv[XH][MB][4];
 #pragma unroll
     for (int h = 0; h < XH; ++h)
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xv[h][mb][j] = xs[u][kh][h * 8 + mb * 4 + j][lane];
+        for (int j = 0; j < 4; ++j) xv[h][mb][j] = xs[u][kh][(h * MB + mb) * 4 + j][lane];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(64 * WN * KS) void gemm_kernel(GemmArgs a) {
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
+          for (int mb = 0; mb < MB; ++mb)
             acc[b][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wb[u][b][j]), as_bf16x8(xv[h][mb][j]),
                                                                  acc[b][mb], 0, 0, 0);
   };
@@ -159,21 +162,63 @@ __global__ __launch_bounds__(64 * WN * KS) void gemm_kernel(GemmArgs a) {
     ks_merge<NB, WN, KS>(acc, reinterpret_cast<float*>(&xs[0][0][0][0]), kh, wc, lane);
     if (kh != 0) return;
   }
-  gemm_epilogue<EPI, NB, WN>(a, acc, e, m_tile, wg, wc, zsplit, rows_e, lane);
+  gemm_epilogue<EPI, NB, WN>(a, acc, e, m_tile * 64 + mb0 * 32, wg, wc, zsplit, rows_e, lane);
+}
+
+enum GemmRows { FULL_TILES, HALF_TILE, BY_COUNT };
+
+template <int EPI, int NB, int WN, int PF, int KS, bool XLO, bool NT_W, int ROWS>
+__global__ __launch_bounds__(64 * WN * KS) void gemm_kernel(GemmArgs a) {
+  __shared__ u32x4 ring[kRingPieces<PF, KS, XLO, ROWS == HALF_TILE ? 1 : 2>][64];
+  stamp_begin(a.stamp);
+  const int e = blockIdx.y;
+  // XCD-aware decode: workgroups are dispatched round-robin over the 8 XCDs
+  // (linear id % 8, and the grid's x extent is a multiple of 8), so the
+  // workgroups of the row tiles that stream the same weights get the same
+  // id % 8 and the re-reads of those weights hit that XCD's L2.
+  int m_tile = 0, wg = blockIdx.x;
+  if (a.m_tiles > 1) {
+    const int grp = blockIdx.x / (8 * a.m_tiles), r = blockIdx.x % (8 * a.m_tiles);
+    m_tile = r >> 3;
+    wg = grp * 8 + (r & 7);
+    if (wg >= a.n_wgs) return;  // padding of the grid to a multiple of 8 (uniform)
+  }
+  const int rows_e = ROWS == BY_COUNT ? a.count[e] : a.m_tiles * 64;
+  if (m_tile * 64 >= rows_e) return;  // uniform over the workgroup
+  u32x4* r0 = &ring[0][0];
+  if constexpr (ROWS == HALF_TILE) {
+    gemm_body<EPI, NB, WN, PF, KS, XLO, NT_W, 1>(a, r0, e, m_tile, a.half - 1, wg, rows_e);
+  } else {
+    if (ROWS == BY_COUNT && rows_e - m_tile * 64 <= 32)  // uniform
+      gemm_body<EPI, NB, WN, PF, KS, XLO, NT_W, 1>(a, r0, e, m_tile, 0, wg, rows_e);
+    else
+      gemm_body<EPI, NB, WN, PF, KS, XLO, NT_W, 2>(a, r0, e, m_tile, 0, wg, rows_e);
+  }
   stamp_end(a.stamp);
+}
+
+template <int EPI, int NB, int WN, int PF, int KS, bool XLO, bool NT_W, int ROWS>
+static hipError_t launch_rows(const GemmArgs& a, int experts, hipStream_t s) {
+  const int gx = a.m_tiles > 1 ? (a.n_wgs + 7) / 8 * 8 * a.m_tiles : a.n_wgs;
+  dim3 grid(gx, experts, a.splits / KS);
+  hipLaunchKernelGGL((gemm_kernel<EPI, NB, WN, PF, KS, XLO, NT_W, ROWS>), grid, dim3(64 * WN * KS), 0, s, a);
+  return hipGetLastError();
 }
 
 template <int EPI, int NB, int WN, int PF, int KS, bool XLO, bool NT_W>
 static hipError_t launch_one(const GemmArgs& a, int experts, hipStream_t s) {
-  const int gx = a.m_tiles > 1 ? (a.n_wgs + 7) / 8 * 8 * a.m_tiles : a.n_wgs;
-  dim3 grid(gx, experts, a.splits / KS);
-  hipLaunchKernelGGL((gemm_kernel<EPI, NB, WN, PF, KS, XLO, NT_W>), grid, dim3(64 * WN * KS), 0, s, a);
-  return hipGetLastError();
+  if (a.count) {  // experts: no LM head
+    if constexpr (EPI != EPI_ARGMAX) return launch_rows<EPI, NB, WN, PF, KS, XLO, NT_W, BY_COUNT>(a, experts, s);
+    return hipErrorInvalidValue;
+  }
+  if (a.half) return launch_rows<EPI, NB, WN, PF, KS, XLO, NT_W, HALF_TILE>(a, experts, s);
+  return launch_rows<EPI, NB, WN, PF, KS, XLO, NT_W, FULL_TILES>(a, experts, s);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, int experts, hipStream_t s) {
   const int epi = a.epi, nb = a.nb, wn = a.wn, pf = a.pf, ks = a.kslices;
   if (ks < 1 || a.splits % ks != 0) return hipErrorInvalidValue;
+  if (a.half < 0 || a.half > 2 || (a.half && (a.m_tiles != 1 || a.count))) return hipErrorInvalidValue;
   // Non-temporal weight loads where they measured faster: the two-slice store
   // form (down) and the LM head (189 -> 182 us).  The one-slice store and the
   // SwiGLU forms measured slower with them.

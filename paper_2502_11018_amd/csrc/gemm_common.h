@@ -8,12 +8,12 @@
 namespace griffin {
 
 // Merge the KS K slices of a workgroup in slice order through LDS (red: at
-// least WN * NB * 8 KB, free: every wave's reads of it have returned).  Every
+// least WN * NB * MB * 4 KB, free: every wave's reads of it have returned).  Every
 // wave of the workgroup calls it (its barriers are uniform); waves whose kh
 // is not a slice index only take part in the barriers.  Slice 0 ends with the
 // sum.
-template <int NB, int WN, int KS>
-__device__ __forceinline__ void ks_merge(f32x16 (&acc)[NB][2], float* red, int kh, int wc, int lane) {
+template <int NB, int WN, int KS, int MB>
+__device__ __forceinline__ void ks_merge(f32x16 (&acc)[NB][MB], float* red, int kh, int wc, int lane) {
   wait_vmcnt_lds<0>();
   __builtin_amdgcn_s_barrier();
   for (int k = 1; k < KS; ++k) {
@@ -21,9 +21,9 @@ __device__ __forceinline__ void ks_merge(f32x16 (&acc)[NB][2], float* red, int k
 #pragma unroll
       for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) red[(((wc * NB + b) * 2 + mb) * 16 + i) * 64 + lane] = acc[b][mb][i];
+          for (int i = 0; i < 16; ++i) red[(((wc * NB + b) * MB + mb) * 16 + i) * 64 + lane] = acc[b][mb][i];
     }
     wait_vmcnt_lds<0>();
     __builtin_amdgcn_s_barrier();
@@ -31,23 +31,23 @@ __device__ __forceinline__ void ks_merge(f32x16 (&acc)[NB][2], float* red, int k
 #pragma unroll
       for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[b][mb][i] += red[(((wc * NB + b) * 2 + mb) * 16 + i) * 64 + lane];
+          for (int i = 0; i < 16; ++i) acc[b][mb][i] += red[(((wc * NB + b) * MB + mb) * 16 + i) * 64 + lane];
     }
     wait_vmcnt_lds<0>();
     __builtin_amdgcn_s_barrier();
   }
 }
 
-// The epilogues, every wave for its own NB column blocks of one 64-row tile.
-template <int EPI, int NB, int WN>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NB][2], int e, int m_tile, int wg,
+// The epilogues, every wave for its own NB column blocks of the 32 MB rows from row0.
+template <int EPI, int NB, int WN, int MB>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NB][MB], int e, int row0, int wg,
                                               int wc, int zsplit, int rows_e, int lane) {
   const int lr = lane & 31, g = lane >> 5;
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb) {
-    const int ml = m_tile * 64 + mb * 32 + lr;  // tile row
+  for (int mb = 0; mb < MB; ++mb) {
+    const int ml = row0 + mb * 32 + lr;  // row of the (expert's) operand
     const bool row_ok = ml < rows_e;
     const long long orow = (long long)e * a.o_erows + ml;
     if constexpr (EPI == EPI_STORE) {
@@ -73,6 +73,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[N
         for (int rg = 0; rg < 4; ++rg) {
           const int n = ((wg * WN + wc) * HB + hb) * 32 + 8 * rg + 4 * g;
           if (n < a.N) {
+            // the product rounds before its split into hi + lo: contracted into
+            // the subtraction, or not, as the compiler chooses per kernel form,
+            // a row's bits would depend on the form that computed it
+#pragma clang fp contract(off)
             float h[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) h[i] = silu_f32(acc[hb][mb][4 * rg + i]) * acc[hb + HB][mb][4 * rg + i];

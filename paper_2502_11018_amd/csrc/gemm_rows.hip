@@ -176,7 +176,7 @@ __global__ __launch_bounds__(512, 2) void gemm_rows_kernel(GemmArgs a) {
     if (kh != 0) return;
   }
   if (tile0 + wm < a.m_tiles)
-    gemm_epilogue<EPI, 4, 1>(a, acc, 0, tile0 + wm, wg * WN + wn, 0, zsplit, a.m_tiles * 64, lane);
+    gemm_epilogue<EPI, 4, 1>(a, acc, 0, (tile0 + wm) * 64, wg * WN + wn, 0, zsplit, a.m_tiles * 64, lane);
   stamp_end(a.stamp);
 }
 

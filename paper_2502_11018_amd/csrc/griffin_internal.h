@@ -72,6 +72,7 @@ struct GemmArgs {
   int x_ks;                  // K steps per activation tile
   int xlo;                   // 1: activations as bf16 hi + lo (fp32-grade); 0: the bf16 hi part alone
   int x_etiles;              // MoE: activation tiles per expert (0 for dense)
+  int half;                  // one row tile: 0 all 64 rows, 1 rows 0-31 alone, 2 rows 32-63 alone (gemm.hip, dense)
   const int32_t* count;      // MoE: [E] valid rows per expert; NULL = m_tiles * 64
   const uint16_t* W;         // packed weights (+ e * w_estride)
   long long w_estride;
@@ -173,13 +174,14 @@ hipError_t launch_gemm(const GemmArgs& a, int experts, hipStream_t s);
 hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
 hipError_t launch_pack_weight(const uint16_t* src, int rows, int K, const PackShape& p, uint16_t* dst,
                               hipStream_t s);
+// The row-wise kernels work on `rows` rows from row0 on.
 hipError_t launch_embed(const uint16_t* embed, const int32_t* token, int rows, int d, float* x, hipStream_t s);
 hipError_t launch_residual_rmsnorm(float* x, const ResidualAdd& add, const uint16_t* gain, float eps,
                                    int rows, int d, uint16_t* xn, int xn_ks, hipStream_t s,
-                                   const Router& route = Router{});
+                                   const Router& route = Router{}, int row0 = 0);
 // inv_freq: [dh / 2] fp64 rotary frequencies base^(-2j/dh)
 hipError_t launch_qkv_rope(const float* qkv_parts, int n_parts, long long part_stride, StepMeta meta,
-                           const double* inv_freq, int Hq, int Hkv, int dh, int max_tree, int batch, int kv_cap,
+                           const double* inv_freq, int Hq, int Hkv, int dh, int max_tree, int row0, int rows, int kv_cap,
                            uint16_t* q_out, uint16_t* q_lo, uint16_t* k_cache_l, uint16_t* v_cache_l, TreeKV32 tree,
                            hipStream_t s);
 hipError_t launch_attention(const AttnArgs& a, int batch, hipStream_t s);
@@ -193,7 +195,7 @@ struct AttnShape {
 };
 AttnShape attn_shape(int group, int max_tree);
 hipError_t launch_attn_combine(const float* part_o, const float* part_ml, StepMeta meta, int Hq, int Hkv, int dh,
-                               int slots, int sp, int qrows, int max_tree, int batch, const uint16_t* q,
+                               int slots, int sp, int qrows, int max_tree, int row0, int rows, const uint16_t* q,
                                const uint16_t* q_lo, TreeKV32 tree, PrefixKV prefix, float scale_log2,
                                uint16_t* o_out, int o_ks, hipStream_t s);
 hipError_t launch_argmax_reduce(const float* pmax, const float* pmax2, const int32_t* pidx, const int32_t* pnan,

@@ -176,6 +176,7 @@ struct griffin_ctx {
 
   int R = 0, Mpad = 0, qkv_n = 0, attn_w = 0, attn_splits = 1, attn_sp = 1, qblocks = 1;
   int comb_slots = 1;  // partial slots the merge reads this step (<= attn_sp)
+  int half = 0;        // rows a pass works on: 0 all, 1 rows 0-31, 2 rows 32-63 (row_half)
   int E = 1, topk = 1;
   long long parts_elems = 0;
 
@@ -227,6 +228,7 @@ struct griffin_ctx {
     bool kv_only;
     int tree_k, tree_depth, tree_n;  // 0: one pass
     int slots;                       // partial slots the merge reads
+    int half;                        // griffin_ctx::half (a draft tree's passes set their own)
     hipGraphExec_t exec;
   };
   std::vector<GraphEntry> graphs;
@@ -368,11 +370,24 @@ unsigned long long* stamp_slot(griffin_ctx* c, int cls) {
     if (prof_) HIP_TRY(c, hipEventRecord(ev1_, c->stream));                 \
   } while (0)
 
+// The row half that holds rows [lo, hi) of a context with one row tile (1 or 2),
+// or 0 for all rows.  A half tile stages and multiplies half of the
+// activations (gemm.hip), and the row-wise kernels launch half of the
+// workgroups.  Every row is computed from its own operands in the same order
+// either way, so results keep their bits.
+int row_half(const griffin_ctx* c, int lo, int hi) {
+  if (c->Mpad != 64) return 0;
+  return hi <= 32 ? 1 : lo >= 32 ? 2 : 0;
+}
+
 int enqueue_pass(griffin_ctx* c, float* logits_out) {
   const griffin_model_desc& d = c->d;
   const int B = c->batch;
   const int rows = B * d.max_tree;
   const int Mpad = round_up(rows, 64);
+  const int row0 = c->half == 2 ? 32 : 0;          // the rows this pass works on: [row0, row0 + nr),
+  const int nr = c->half ? 32 : Mpad;              // padding included,
+  const int nlive = std::min(rows, row0 + nr) - row0;  // and without it
   const int m_tiles = Mpad / 64;
   const long long ps = (long long)Mpad;  // rows per split slice of `parts`
   hipStream_t s = c->stream;
@@ -382,7 +397,7 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
   if (c->front)
     TRY(c->front(c, s));
   else
-    LAUNCH(GRIFFIN_KC_NORM, launch_embed(c->embed, c->meta.token, Mpad, d.d_model, c->x, s));
+    LAUNCH(GRIFFIN_KC_NORM, launch_embed(c->embed, c->meta.token, nr, d.d_model, c->x, s));
   ResidualAdd none{};
   ResidualAdd add_down{};
   for (int l = 0; l < d.n_layers; ++l) {
@@ -393,9 +408,10 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
       clear.n_clear = c->E;
     }
     LAUNCH(GRIFFIN_KC_NORM, launch_residual_rmsnorm(c->x, l == 0 ? none : add_down, c->attn_norm[l], d.rms_eps,
-                                                    Mpad, d.d_model, c->xn, c->xd_ks, s, clear));
+                                                    nr, d.d_model, c->xn, c->xd_ks, s, clear, row0));
     {
       GemmArgs a = gemm_args(c->p_qkv, c->xn, c->xd_ks, c->pk_qkv[l], m_tiles, !c->act_bf16);
+      a.half = c->half;
       a.out = c->parts;
       a.ldo = c->qkv_n;
       a.out_split_stride = ps * c->qkv_n;
@@ -405,8 +421,8 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
     uint16_t* kc = c->k_cache + (size_t)l * layer_kv;
     uint16_t* vc = c->v_cache + (size_t)l * layer_kv;
     LAUNCH(GRIFFIN_KC_ROPE, launch_qkv_rope(c->parts, c->p_qkv.out_splits(m_tiles), ps * c->qkv_n, c->meta, c->rope_inv,
-                                            d.n_q_heads, d.n_kv_heads, d.head_dim, d.max_tree, B, d.kv_capacity,
-                                            c->q, c->q_lo, kc, vc, c->tree, s));
+                                            d.n_q_heads, d.n_kv_heads, d.head_dim, d.max_tree, row0, nlive,
+                                            d.kv_capacity, c->q, c->q_lo, kc, vc, c->tree, s));
     if (c->kv_only && l == d.n_layers - 1) return GRIFFIN_OK;
     {
       AttnArgs a{};
@@ -431,10 +447,11 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
     }
     LAUNCH(GRIFFIN_KC_MERGE, launch_attn_combine(c->attn_po, c->attn_pml, c->meta, d.n_q_heads, d.n_kv_heads,
                                                 d.head_dim, c->comb_slots, c->attn_sp, c->qblocks * 32, d.max_tree,
-                                                B, c->q, c->q_lo, c->tree, PrefixKV{kc, vc, d.kv_capacity},
+                                                row0, nlive, c->q, c->q_lo, c->tree, PrefixKV{kc, vc, d.kv_capacity},
                                                 scale_log2, c->o, c->p_o.ks_pad, s));
     {
       GemmArgs a = gemm_args(c->p_o, c->o, c->p_o.ks_pad, c->pk_o[l], m_tiles, !c->act_bf16);
+      a.half = c->half;
       a.out = c->parts;
       a.ldo = d.d_model;
       a.out_split_stride = ps * d.d_model;
@@ -463,17 +480,19 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
       route.cap = Mpad;
       route.padded_rows = Mpad;
     }
-    LAUNCH(GRIFFIN_KC_NORM, launch_residual_rmsnorm(c->x, add_o, c->mlp_norm[l], d.rms_eps, Mpad, d.d_model, c->xn,
-                                                    c->xd_ks, s, route));
+    LAUNCH(GRIFFIN_KC_NORM, launch_residual_rmsnorm(c->x, add_o, c->mlp_norm[l], d.rms_eps, nr, d.d_model, c->xn,
+                                                    c->xd_ks, s, route, row0));
 
     // ---- MLP block
     if (c->E == 1) {
       GemmArgs g = gemm_args(c->p_gu, c->xn, c->xd_ks, c->pk_gu[l], m_tiles, !c->act_bf16);
+      g.half = c->half;
       g.act = c->act;
       g.act_ks = c->p_down.ks_pad;
       g.stamp = stamp_slot(c, GRIFFIN_KC_GATE_UP);
       LAUNCH(GRIFFIN_KC_GATE_UP, launch_plan(c->p_gu, g, 1, s));
       GemmArgs dn = gemm_args(c->p_down, c->act, c->p_down.ks_pad, c->pk_down[l], m_tiles, !c->act_bf16);
+      dn.half = c->half;
       dn.out = c->parts;
       dn.ldo = d.d_model;
       dn.out_split_stride = ps * d.d_model;
@@ -517,11 +536,12 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
   if (c->back)
     TRY(c->back(c, add_down, s));
   else
-    LAUNCH(GRIFFIN_KC_NORM, launch_residual_rmsnorm(c->x, add_down, c->final_norm, d.rms_eps, Mpad, d.d_model,
-                                                    c->xn, c->xd_ks, s));
+    LAUNCH(GRIFFIN_KC_NORM, launch_residual_rmsnorm(c->x, add_down, c->final_norm, d.rms_eps, nr, d.d_model,
+                                                    c->xn, c->xd_ks, s, Router{}, row0));
   const int lm_parts = c->p_lm.shape.n_wgs * c->p_lm.wn;
   {
     GemmArgs a = gemm_args(c->p_lm, c->xn, c->xd_ks, c->pk_lm, m_tiles, !c->act_bf16);
+    a.half = c->half;
     a.pmax = c->pmax;
     a.pmax2 = c->pmax2;
     a.pidx = c->pidx;
@@ -534,7 +554,7 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
     LAUNCH(GRIFFIN_KC_LM_HEAD, launch_plan(c->p_lm, a, 1, s));
   }
   if (c->front) return GRIFFIN_OK;  // a draft pass: the caller reads the logits
-  LAUNCH(GRIFFIN_KC_OTHER, launch_argmax_reduce(c->pmax, c->pmax2, c->pidx, c->pnan, lm_parts, lm_parts, rows,
+  LAUNCH(GRIFFIN_KC_OTHER, launch_argmax_reduce(c->pmax, c->pmax2, c->pidx, c->pnan, lm_parts, lm_parts, nlive,
                                                 c->pred, c->margin, c->nan_row, s));
   LAUNCH(GRIFFIN_KC_OTHER, launch_accept(c->meta, c->pred, c->nan_row, B, d.max_tree, d.max_depth, c->result, s));
   return GRIFFIN_OK;
@@ -552,7 +572,8 @@ int run_graph(griffin_ctx* c, const griffin_ctx::GraphEntry& key, Body body) {
   if (!c->use_graphs || c->prof_mask != 0 || c->stream == nullptr) return body();
   for (auto& g : c->graphs)
     if (g.batch == key.batch && g.logits == key.logits && g.kv_only == key.kv_only && g.tree_k == key.tree_k &&
-        g.tree_depth == key.tree_depth && g.tree_n == key.tree_n && g.slots == key.slots) {
+        g.tree_depth == key.tree_depth && g.tree_n == key.tree_n && g.slots == key.slots &&
+        g.half == key.half) {
       HIP_TRY(c, hipGraphLaunch(g.exec, c->stream));
       return GRIFFIN_OK;
     }
@@ -582,7 +603,7 @@ int run_graph(griffin_ctx* c, const griffin_ctx::GraphEntry& key, Body body) {
 
 // One pass (batch, logits_out, kv_only from the context).
 int run_pass(griffin_ctx* c, float* logits_out) {
-  return run_graph(c, {c->batch, logits_out, c->kv_only, 0, 0, 0, c->comb_slots, nullptr},
+  return run_graph(c, {c->batch, logits_out, c->kv_only, 0, 0, 0, c->comb_slots, c->half, nullptr},
                    [&]() { return enqueue_pass(c, logits_out); });
 }
 
@@ -629,7 +650,8 @@ DraftArgs draft_args(griffin_draft* dc, griffin_ctx* c) {
   a.d = dc->d;
   a.tgf_dim = dc->e;
   a.rows = rows;
-  a.mpad = mpad;
+  a.row0 = c->half == 2 ? 32 : 0;
+  a.nr = c->half ? 32 : mpad;
   a.max_tree = d.max_tree;
   a.ln_eps = dc->ln_eps;
   a.rms_eps = d.rms_eps;
@@ -676,6 +698,7 @@ hipError_t draft_gemm(griffin_draft* dc, griffin_ctx* c, const GemmPlan& p, cons
                       int N, hipStream_t s) {
   const int mpad = round_up(c->batch * c->d.max_tree, 64);
   GemmArgs a = gemm_args(p, X, p.ks_pad, W, mpad / 64, !c->act_bf16);
+  a.half = c->half;
   a.out = dc->parts;
   a.ldo = N;
   a.out_split_stride = (long long)mpad * N;
@@ -1018,6 +1041,9 @@ int griffin_verify_step(griffin_ctx* c, int32_t batch, const int32_t* prefix_len
       h_parent[r0 + i] = i == 0 ? 0 : parents[r0 + i];
     }
   }
+  int last = 0;  // one past the last live row
+  for (int b = 0; b < batch; ++b) last = b * d.max_tree + n_nodes[b];
+  c->half = row_half(c, 0, last);
   attn_split_plan(batch, prefix_len, n_nodes, c->attn_splits, c->attn_sp,
                   reinterpret_cast<int32_t*>(h + c->off_split), reinterpret_cast<int32_t*>(h + c->off_nsplit));
   c->comb_slots = c->meta.split_tab ? merge_slots(reinterpret_cast<const int32_t*>(h + c->off_nsplit), batch, c->attn_sp)
@@ -1656,7 +1682,7 @@ int griffin_draft_step(griffin_draft* dc, int32_t batch, const int32_t* prefix_l
                             c->stream));
   TRY(griffin_verify_step(c, batch, prefix_len, n_nodes, tokens, parents, dc->logits));
   const int rows = batch * d.max_tree;
-  HIP_TRY(c, launch_draft_topk(dc->logits, d.vocab, d.vocab, c->meta, rows, d.max_tree, k, dc->topk_tok,
+  HIP_TRY(c, launch_draft_topk(dc->logits, d.vocab, d.vocab, c->meta, rows, d.max_tree, 0, d.max_tree, k, dc->topk_tok,
                                dc->topk_lp, dc->topk_work, c->stream));
   HIP_TRY(c, hipMemcpyAsync(dc->topk_tok_host, dc->topk_tok, sizeof(int32_t) * rows * k, hipMemcpyDeviceToHost,
                             c->stream));
@@ -1784,11 +1810,16 @@ int griffin_draft_tree(griffin_draft* dc, int32_t batch, const int32_t* prefix_l
   // the whole expansion, every pass with its top-k and selection, is one graph
   // the passes' split plans differ, so the merge reads every slot
   c->comb_slots = c->attn_sp;
-  TRY(run_graph(c, {batch, dc->logits, false, k, depth, n_total, c->comb_slots, nullptr}, [&]() -> int {
+  TRY(run_graph(c, {batch, dc->logits, false, k, depth, n_total, c->comb_slots, 0, nullptr}, [&]() -> int {
     for (int t = 0; t < depth; ++t) {
+      // a pass works on the row half its new nodes are in (both where they
+      // straddle); the nodes before them keep the K/V and the regress features
+      // of their own pass, which recomputing them would only repeat
+      const int f0 = t == 0 ? 0 : 1 + k * (t - 1), nf = t == 0 ? 1 : k;
+      c->half = row_half(c, f0, (batch - 1) * T + f0 + nf);
       TRY(enqueue_pass(c, dc->logits));
-      HIP_TRY(c, launch_draft_topk(dc->logits, d.vocab, d.vocab, c->meta, rows, T, k, dc->topk_tok, dc->topk_lp,
-                                   dc->topk_work, c->stream));
+      HIP_TRY(c, launch_draft_topk(dc->logits, d.vocab, d.vocab, c->meta, rows, T, f0, nf, k, dc->topk_tok,
+                                   dc->topk_lp, dc->topk_work, c->stream));
       sa.t = t;
       const bool more = t + 1 < depth;
       sa.tail_src = more ? reinterpret_cast<const uint4*>(dc->stage_dev + tail * t) : nullptr;

@@ -312,6 +312,31 @@ def test_device_expansion_equals_host_expansion_of_its_passes(name, k, D, N):
         dr.close()
 
 
+@pytest.mark.parametrize("name,B,max_tree,k,D,N", [
+    ("small-gqa", 1, 64, 10, 6, 60),    # passes in rows 0-31, one over both halves, one in rows 32-63
+    ("tiny-v20000", 1, 64, 16, 4, 63),  # node 32 ends a frontier that begins in the lower half
+    ("tiny", 2, 32, 5, 6, 31)])         # two sequences, one per half
+def test_expansion_over_half_tiles_equals_whole_passes(name, B, max_tree, k, D, N):
+    """A tree's passes recompute only the row half of their new nodes where that
+    half holds them all; the host expansion recomputes every node in every
+    pass.  Trees, scores and the cached K/V must agree bit for bit."""
+    prefix = [61, 33][:B]
+    dr = Draft(name, B, prefix, max_tree)
+    try:
+        say(f"draft {name}: half tiles batch {B} max_tree {max_tree} k={k} depth={D}")
+        roots, feat = [5, 17][:B], dr.feat.cuda()
+        n, tok, par, sc = dr.dm.tree(prefix, roots, feat, k, D, N)
+        torch.cuda.synchronize()
+        kc, vc = dr.dm.k_cache.clone(), dr.dm.v_cache.clone()
+        for b, (rt, rp, rs) in enumerate(_host_expansion(dr.dm, prefix, roots, feat, k, D, N)):
+            assert tok[b, : n[b]].tolist() == rt and par[b, : n[b]].tolist() == rp, b
+            assert np.array_equal(sc[b, : n[b]], rs), b
+        torch.cuda.synchronize()
+        assert torch.equal(kc, dr.dm.k_cache) and torch.equal(vc, dr.dm.v_cache)
+    finally:
+        dr.close()
+
+
 def test_draft_errors():
     import paper_2502_11018_amd as P
     dr = Draft("tiny", 1, [30], max_tree=16)
