@@ -29,13 +29,19 @@
 // rejections before it at the same node, so all nodes advance together, one
 // launch per child rank, each spreading a node's vocabulary over `nslice`
 // workgroups that write per-slice partial sums:
-//   sampled_norm_kernel: softmax normaliser and sum of q (partials);
+//   sampled_norm_kernel: softmax normaliser and sum of q (partials) of the
+//     nodes with children (a leaf matters only where a walk ends: its partials
+//     come from the draw launch; 244 nodes x 128256: 55 -> 23 us);
 //   sampled_step_kernel, k = 0, 1, ..: every workgroup first folds the
 //     previous launch's partials into the node's state (in slice order; the
 //     same arithmetic in every workgroup, workgroup 0 stores it), takes the
-//     k-th child's acceptance probability, then reduces G for its rejection;
+//     k-th child's acceptance probability, then reduces G for its rejection
+//     unless the child is accepted (its later siblings are never tested, so
+//     the node's remaining launches leave at once; the case above, ten
+//     launches: 87 -> 48 us);
 //   sampled_draw_sums_kernel: walks every tree with the stored probabilities,
-//     folds the final node's last partials, sums its residual per slice;
+//     folds the final node's last partials, sums its residual per slice (a
+//     leaf: its softmax partials, which are its sums);
 //   sampled_pick_kernel: the inverse CDF: the slice that holds u * total,
 //     then an exact in-order scan inside it.
 // Kernel boundaries order every hand-over; no counters, fences or atomics.
@@ -65,8 +71,11 @@ constexpr int SA_RM = 64;  // rejected tokens per node (children: max_tree - 1 <
 struct SampState {
   float M, inv_z, inv_q;  // max logit, 1 / softmax normaliser, 1 / sum(q)
   float a, D, S;          // residual parameters and q mass left
-  int n_rm, bad;          // rejected tokens so far; NaN in the logits or no mass
+  int n_rm, bad;          // rejected tokens so far; BAD, DONE
 };
+
+constexpr int BAD = 1;   // NaN in the logits or no mass
+constexpr int DONE = 2;  // a child was accepted
 
 struct RmEntry {
   int tok;
@@ -131,17 +140,6 @@ __device__ __forceinline__ float resid(float x, float y, float a, const Norm& n)
 
 __device__ __forceinline__ Norm norm_of(const SampState& s, float inv_t) { return {s.M, inv_t, s.inv_z, s.inv_q}; }
 
-__device__ __forceinline__ float block_max(float v, float* smem) {
-  v = wave_max(v);
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) smem[w] = v;
-  __syncthreads();
-  float t = -INFINITY;
-  for (int i = 0; i < nw; ++i) t = fmaxf(t, smem[i]);
-  return t;
-}
-
 // Slice s of a row: a multiple of 4 elements long, so that with V % 4 == 0
 // every slice starts on a 16-byte boundary of the row.
 __device__ __forceinline__ void slice_range(int V, int nslice, int s, int& lo, int& hi) {
@@ -189,7 +187,7 @@ __device__ __forceinline__ SampState state_from_norm(float4 pp, float inv_t) {
   st.D = 1.f;
   st.S = 1.f;
   st.n_rm = 0;
-  st.bad = (anybad > 0.f || !(Z > 0.f)) ? 1 : 0;
+  st.bad = (anybad > 0.f || !(Z > 0.f)) ? BAD : 0;
   return st;
 }
 
@@ -228,37 +226,79 @@ __device__ __forceinline__ float accept_prob(const SampState& st, const RmEntry&
   return q_res > 0.f ? fminf(1.f, p_res / q_res) : (p_res > 0.f ? 1.f : 0.f);
 }
 
-// ---- softmax normaliser and q's sum of every node --------------------------------
+// ---- softmax normaliser and q's sum of a node, per slice -------------------------
+// Running maximum and sum of exp((x - m) / T); -inf logits add nothing, NaN
+// ones are flagged (fmaxf skips them).  Eight elements a thread at a time: all
+// loads first, one rescale per eight, one exponential per element.  Thread 0
+// gets the slice's (maximum, sum, q sum, NaN flag); red: 4 floats per wave.
+template <bool VEC, bool Q>
+__device__ __forceinline__ float4 slice_norm(const float* lg, const float* qd, int lo, int hi, float inv_t,
+                                             float4* red) {
+  const int tid = threadIdx.x;
+  float m = -INFINITY, se = 0.f, sq = 0.f;
+  bool bad = false;
+  for (int base = lo; base < hi; base += 8 * SA_THREADS) {  // uniform
+    float x[8], y[8];
+    if constexpr (VEC) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int at = base + 4 * (tid + h * SA_THREADS);
+        const bool in = at < hi;  // slices start and end on multiples of 4
+        const float4 xv = in ? *reinterpret_cast<const float4*>(lg + at)
+                             : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        const float4 yv = Q && in ? *reinterpret_cast<const float4*>(qd + at) : make_float4(0.f, 0.f, 0.f, 0.f);
+        x[4 * h] = xv.x; x[4 * h + 1] = xv.y; x[4 * h + 2] = xv.z; x[4 * h + 3] = xv.w;
+        y[4 * h] = yv.x; y[4 * h + 1] = yv.y; y[4 * h + 2] = yv.z; y[4 * h + 3] = yv.w;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int at = base + tid + u * SA_THREADS;
+        x[u] = at < hi ? lg[at] : -INFINITY;
+        y[u] = Q && at < hi ? qd[at] : 0.f;
+      }
+    }
+    float mn = m;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      mn = fmaxf(mn, x[u]);
+      bad |= x[u] != x[u];
+      sq += y[u];
+    }
+    if (mn > m) se *= expf((m - mn) * inv_t);
+    m = mn;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) se += x[u] > -INFINITY ? expf((x[u] - mn) * inv_t) : 0.f;
+  }
+  const float mw = wave_max(m);
+  const float sw = wave_sum(m > -INFINITY ? se * expf((m - mw) * inv_t) : 0.f);
+  const float qw = wave_sum(sq);
+  const float bw = wave_max(bad ? 1.f : 0.f);
+  __syncthreads();
+  if ((tid & 63) == 0) red[tid >> 6] = make_float4(mw, sw, qw, bw);
+  __syncthreads();
+  float4 r = red[0];
+  for (int w = 1; w < SA_THREADS / 64; ++w) r.x = fmaxf(r.x, red[w].x);
+  r.y = 0.f;
+  for (int w = 0; w < SA_THREADS / 64; ++w) r.y += red[w].x > -INFINITY ? red[w].y * expf((red[w].x - r.x) * inv_t) : 0.f;
+  for (int w = 1; w < SA_THREADS / 64; ++w) {
+    r.z += red[w].z;
+    r.w = fmaxf(r.w, red[w].w);
+  }
+  return r;
+}
+
 template <bool VEC>
-__global__ __launch_bounds__(SA_THREADS) void sampled_norm_kernel(SampledArgs a, int nslice, int n_parents) {
-  __shared__ float red[8];
+__global__ __launch_bounds__(SA_THREADS) void sampled_norm_kernel(SampledArgs a, int nslice) {
+  __shared__ float4 red[SA_THREADS / 64];
   const SampScratch sc = sa_carve(a.scratch, a.scratch_batch, a.max_tree, nslice);
-  const int s = blockIdx.x, row = a.order[blockIdx.y], tid = threadIdx.x, V = a.vocab;
+  const int s = blockIdx.x, row = a.order[blockIdx.y], V = a.vocab;
   const float* lg = a.logits + (size_t)row * V;
-  const float* qd = a.q ? a.q + (size_t)row * V : nullptr;
-  const float inv_t = a.inv_t;
   int lo, hi;
   slice_range(V, nslice, s, lo, hi);
-  // running maximum and sum of exp((x - m) / T); -inf logits add nothing, NaN
-  // ones are flagged (fmaxf skips them)
-  float m = -INFINITY, se = 0.f, sq = 0.f;
-  int bad = 0;
-  auto f = [&](float x, float y) {
-    sq += y;
-    bad |= x != x;
-    const float mn = fmaxf(m, x);
-    se = (mn == m ? se : se * expf((m - mn) * inv_t)) + (x > -INFINITY ? expf((x - mn) * inv_t) : 0.f);
-    m = mn;
-  };
-  if (qd && (int)blockIdx.y < n_parents)  // rows of `order` with children come first
-    for_slice<VEC, true>(lg, qd, lo, hi, f);
-  else
-    for_slice<VEC, false>(lg, qd, lo, hi, f);
-  const float mb = block_max(m, red);
-  const float seb = block_sum(m > -INFINITY ? se * expf((m - mb) * inv_t) : 0.f, red);
-  const float sqb = block_sum(sq, red);
-  const float badb = block_max((float)bad, red);
-  if (tid == 0) sc.npart[(size_t)row * nslice + s] = make_float4(mb, seb, sqb, badb);
+  const float4 r = a.q ? slice_norm<VEC, true>(lg, a.q + (size_t)row * V, lo, hi, a.inv_t, red)
+                       : slice_norm<VEC, false>(lg, nullptr, lo, hi, a.inv_t, red);
+  if (threadIdx.x == 0) sc.npart[(size_t)row * nslice + s] = r;
 }
 
 // ---- the k-th child of every node with more than k children ----------------------
@@ -275,6 +315,16 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_step_kernel(SampledArgs a,
   const float* lg = a.logits + (size_t)row * V;
   const float* qd = a.q + (size_t)row * V;
   const size_t rows = (size_t)a.scratch_batch * a.max_tree;
+  if (k > 0) {
+    const SampState* prev = sc.st + ((k - 1) & 1) * rows + row;
+    if (prev->bad & DONE) {  // uniform: an earlier child was accepted
+      if (s == 0 && tid == 0) {
+        sc.st[(k & 1) * rows + row].bad = DONE;
+        sc.acc[(size_t)(row / a.max_tree) * a.max_tree + a.step_child[base + item]] = 0.f;
+      }
+      return;
+    }
+  }
   if (tid < 64) {
     const int lane = tid;
     const int t = a.step_token[base + item], child = a.step_child[base + item];
@@ -297,10 +347,13 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_step_kernel(SampledArgs a,
     }
     const Norm nm = norm_of(st, a.inv_t);
     const float acc = accept_prob(st, e, t, p_of(x, nm), y * nm.inv_q);
+    const size_t crow = (size_t)(row / a.max_tree) * a.max_tree + child;
+    const int nan = st.bad;
+    if (a.u_accept[crow] < acc) st.bad |= DONE;
     if (s == 0 && lane == 0) {
       sc.st[(k & 1) * rows + row] = st;
-      sc.acc[(size_t)(row / a.max_tree) * a.max_tree + child] = acc;
-      if (k == 0) sc.bad[row] = st.bad;
+      sc.acc[crow] = acc;
+      if (k == 0) sc.bad[row] = nan;
     }
     if (lane == 0) sh_st = st;
   }
@@ -320,6 +373,7 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_step_kernel(SampledArgs a,
 // ---- the walk and the final node's state (one wave; every workgroup alike) -------
 struct WalkEnd {
   int node, L, nan, pathv;  // pathv: this lane's path entry (lane < L)
+  bool leaf;                // q given and the final node has no children: its partials are the draw launch's
   SampState st;             // final node: state after all its children's rejections
   RmEntry e;                // this lane's rejected-token entry of the final node
 };
@@ -335,6 +389,7 @@ __device__ __forceinline__ WalkEnd walk_tree_point_mass(const SampledArgs& a, co
   const int tok = in ? a.token[row0 + ln] : 0;
   const float ua = in ? a.u_accept[row0 + ln] : 1.f;
   WalkEnd w;
+  w.leaf = false;
   w.node = 0;
   w.L = 0;
   w.nan = 0;
@@ -377,6 +432,8 @@ __device__ __forceinline__ WalkEnd walk_tree_point_mass(const SampledArgs& a, co
   }
 }
 
+// LEAF: a leaf's partials are there (the draw launch has written them).
+template <bool LEAF>
 __device__ __forceinline__ WalkEnd walk_tree(const SampledArgs& a, const SampScratch& sc, int nslice, int b) {
   if (!a.q) return walk_tree_point_mass(a, sc, nslice, b);
   const int lane = threadIdx.x & 63, n = a.n_nodes[b];
@@ -388,6 +445,7 @@ __device__ __forceinline__ WalkEnd walk_tree(const SampledArgs& a, const SampScr
   const float ua = in ? a.u_accept[row0 + ln] : 1.f;
   const int badv = in ? sc.bad[row0 + ln] : 0;
   WalkEnd w;
+  w.leaf = false;
   w.node = 0;
   w.L = 0;
   w.nan = 0;
@@ -410,6 +468,9 @@ __device__ __forceinline__ WalkEnd walk_tree(const SampledArgs& a, const SampScr
   const int nk = __popcll(kids);
   w.e = RmEntry{-1, 0.f, 0.f, 0.f};
   if (nk == 0) {
+    w.leaf = true;
+    w.st = SampState{};
+    if (!LEAF) return w;
     const float4 pp = lane < nslice ? sc.npart[fr * nslice + lane] : make_float4(-INFINITY, 0.f, 0.f, 0.f);
     w.st = state_from_norm(pp, a.inv_t);
     w.nan = w.st.bad;
@@ -430,21 +491,31 @@ __device__ __forceinline__ WalkEnd walk_tree(const SampledArgs& a, const SampScr
 template <bool VEC>
 __global__ __launch_bounds__(SA_THREADS) void sampled_draw_sums_kernel(SampledArgs a, int nslice) {
   __shared__ float red[8];
+  __shared__ float4 nred[SA_THREADS / 64];
   __shared__ SampState sh_st;
-  __shared__ int sh_node, sh_nan;
+  __shared__ int sh_node, sh_nan, sh_leaf;
   __shared__ RmEntry rml[SA_RM];
   const SampScratch sc = sa_carve(a.scratch, a.scratch_batch, a.max_tree, nslice);
   const int s = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.vocab;
   if (tid < 64) {
-    const WalkEnd w = walk_tree(a, sc, nslice, b);
+    const WalkEnd w = walk_tree<false>(a, sc, nslice, b);
     if (tid == 0) {
       sh_st = w.st;
       sh_node = w.node;
       sh_nan = w.nan;
+      sh_leaf = w.leaf;
     }
     rml[tid] = w.e;
   }
   __syncthreads();
+  if (sh_leaf) {  // uniform
+    const size_t fr = (size_t)b * a.max_tree + sh_node;
+    int lo, hi;
+    slice_range(V, nslice, s, lo, hi);
+    const float4 r = slice_norm<VEC, false>(a.logits + fr * V, nullptr, lo, hi, a.inv_t, nred);
+    if (tid == 0) sc.npart[fr * nslice + s] = r;
+    return;
+  }
   float g = 0.f;
   if (!sh_nan) {
     const SampState st = sh_st;
@@ -481,10 +552,14 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_pick_kernel(SampledArgs a,
   const size_t row0 = (size_t)b * a.max_tree;
   WalkEnd w;
   if (tid < 64) {
-    w = walk_tree(a, sc, nslice, b);
+    w = walk_tree<true>(a, sc, nslice, b);
     rml[tid] = w.e;
     // inclusive scan of the slice sums, in slice order
-    const float ps = tid < nslice ? sc.dpart[(size_t)b * nslice + tid] : 0.f;
+    float ps = tid < nslice && !w.leaf ? sc.dpart[(size_t)b * nslice + tid] : 0.f;
+    if (w.leaf && tid < nslice) {  // the sum of p over a slice, from its softmax partials
+      const float4 pp = sc.npart[(row0 + w.node) * nslice + tid];
+      ps = pp.x > -INFINITY ? pp.y * expf((pp.x - w.st.M) * a.inv_t) * w.st.inv_z : 0.f;
+    }
     float inc = ps;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -572,8 +647,10 @@ template <bool VEC>
 static void launch_all(const SampledArgs& a, const int* rows_with, int max_children, int ns, hipStream_t s) {
   // a deterministic draft's walk tests the children itself: no step launches
   const int steps = a.q ? max_children : 0;
-  hipLaunchKernelGGL(sampled_norm_kernel<VEC>, dim3(ns, rows_with[0]), dim3(SA_THREADS), 0, s, a, ns,
-                     steps > 0 ? rows_with[1] : 0);
+  // a sampled draft's leaves have no test; rows of `order` with children come first
+  const int normed = !a.q ? rows_with[0] : steps > 0 ? rows_with[1] : 0;
+  if (normed > 0)
+    hipLaunchKernelGGL(sampled_norm_kernel<VEC>, dim3(ns, normed), dim3(SA_THREADS), 0, s, a, ns);
   for (int k = 0, base = 0, prev = 0; k < steps; prev = base, base += rows_with[++k])
     hipLaunchKernelGGL(sampled_step_kernel<VEC>, dim3(ns, rows_with[k + 1]), dim3(SA_THREADS), 0, s, a, ns, k, base,
                        prev);
