@@ -14,6 +14,8 @@ of the oracle's draft (scores, top-k membership, nothing dropped that beats
 the kept nodes by more than SCORE_GAP).  Every case prints its name first.
 """
 
+from dataclasses import replace
+
 import numpy as np
 import pytest
 import torch
@@ -350,3 +352,29 @@ def test_draft_errors():
             dr.dm.step([30], [gen.chain_tree(1, [])], dr.feat[:1], 4)
     finally:
         dr.close()
+
+
+@pytest.mark.parametrize("V,k", [(20000, 16), (20001, 16), (8193, 1), (8192, 10), (16, 16)])
+def test_topk_of_tied_logits(V, k):
+    """Logits that are all equal (the most candidates a slice can have), and
+    logits with a few equal values: value descending, lower id first."""
+    import paper_2502_11018_amd as P
+    ds = replace(DRAFTS["tiny"], target=replace(DRAFTS["tiny"].target, vocab=V))
+    m = ds.target
+    mw, dw = gen.make_weights(m, 0), gen.make_draft_weights(ds, 3)
+    feat = gen.draft_root_features(m.d_model, 1, 11).cuda()
+    row = mw.lm_head[0].clone()
+    level = torch.from_numpy(np.random.default_rng(1).integers(-2, 3, V))
+    for what, lv in (("equal", torch.zeros(V, dtype=torch.int64)), ("levels", level)):
+        say(f"draft top-k of {what} logits, V {V} k {k}")
+        mw.lm_head = row[None, :] * lv[:, None].to(row.dtype)  # exact multiples of one row: ties bit for bit
+        with P.DraftModel(ds, dw.to("cuda"), mw.to("cuda"), max_batch=1, max_tree=16, max_depth=4,
+                          kv_capacity=64) as dm:
+            tok, lp = dm.step([0], [gen.Tree(np.asarray([1], np.int32), np.asarray([-1], np.int32))], feat, k)
+        if what == "equal":
+            assert tok[0, 0].tolist() == list(range(k))
+            assert np.abs(lp[0, 0] + np.log(V)).max() < 1e-4
+        else:  # the sign of the row's product decides which end comes first
+            lv = lv.numpy()
+            assert tok[0, 0].tolist() in (np.argsort(-lv, kind="stable")[:k].tolist(),
+                                          np.argsort(lv, kind="stable")[:k].tolist())
