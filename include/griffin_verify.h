@@ -236,8 +236,9 @@ int griffin_read_router_logits(griffin_ctx *ctx, float *out);
 int griffin_read_features(griffin_ctx *ctx, int32_t batch, int32_t n, const int32_t *nodes, float *out);
 
 /* Replay the launch sequence of a step from a captured HIP graph (default:
- * enabled).  One graph is captured per (batch, logits_out) pair on its first
- * step and replayed afterwards (at most 8 are kept, the oldest is dropped);
+ * enabled).  One graph is captured per (batch, logits_out) pair, and per form of
+ * the launches (live rows in half a row tile or not, key splits to merge), on its first
+ * step and replayed afterwards (at most 16 are kept, the oldest is dropped);
  * every per-step input travels through device buffers whose addresses are
  * fixed for the context, so replays compute exactly what plain launches do.
  * Steps use plain launches while per-class timing is enabled or when the

@@ -565,7 +565,8 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
 // launch kernel by kernel.  Every per-step input lives in device buffers whose
 // addresses are fixed for the context, so a graph stays valid for its key.
 // Per-class timing and the legacy null stream use the plain launches.
-constexpr size_t kMaxGraphs = 8;
+// Twice eight: a loop of steps with few and with many live rows holds a graph for each.
+constexpr size_t kMaxGraphs = 16;
 
 template <class Body>
 int run_graph(griffin_ctx* c, const griffin_ctx::GraphEntry& key, Body body) {
