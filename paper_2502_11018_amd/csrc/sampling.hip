@@ -30,18 +30,20 @@
 // launch per child rank, each spreading a node's vocabulary over `nslice`
 // workgroups that write per-slice partial sums:
 //   sampled_norm_kernel: softmax normaliser and sum of q (partials) of the
-//     nodes with children (a leaf matters only where a walk ends: its partials
-//     come from the draw launch; 244 nodes x 128256: 55 -> 23 us);
+//     nodes with children (a leaf matters only where a walk ends; with the
+//     launches that leave early below, 244 nodes x 128256, the whole call: 201
+//     -> 144 us);
 //   sampled_step_kernel, k = 0, 1, ..: every workgroup first folds the
 //     previous launch's partials into the node's state (in slice order; the
 //     same arithmetic in every workgroup, workgroup 0 stores it), takes the
 //     k-th child's acceptance probability, then reduces G for its rejection
 //     unless the child is accepted (its later siblings are never tested, so
-//     the node's remaining launches leave at once; the case above, ten
+//     the node's remaining launches leave at once; the trees above, ten
 //     launches: 87 -> 48 us);
-//   sampled_draw_sums_kernel: walks every tree with the stored probabilities,
-//     folds the final node's last partials, sums its residual per slice (a
-//     leaf: its softmax partials, which are its sums);
+//   sampled_leaf_norm_kernel: walks every tree with the stored probabilities;
+//     the softmax partials of the leaves where a walk ends;
+//   sampled_draw_sums_kernel: the walk again, folds the final node's last
+//     partials, sums its residual per slice;
 //   sampled_pick_kernel: the inverse CDF: the slice that holds u * total,
 //     then an exact in-order scan inside it.
 // Kernel boundaries order every hand-over; no counters, fences or atomics.
@@ -140,6 +142,17 @@ __device__ __forceinline__ float resid(float x, float y, float a, const Norm& n)
 
 __device__ __forceinline__ Norm norm_of(const SampState& s, float inv_t) { return {s.M, inv_t, s.inv_z, s.inv_q}; }
 
+__device__ __forceinline__ float block_max(float v, float* smem) {
+  v = wave_max(v);
+  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) smem[w] = v;
+  __syncthreads();
+  float t = -INFINITY;
+  for (int i = 0; i < nw; ++i) t = fmaxf(t, smem[i]);
+  return t;
+}
+
 // Slice s of a row: a multiple of 4 elements long, so that with V % 4 == 0
 // every slice starts on a 16-byte boundary of the row.
 __device__ __forceinline__ void slice_range(int V, int nslice, int s, int& lo, int& hi) {
@@ -228,69 +241,36 @@ __device__ __forceinline__ float accept_prob(const SampState& st, const RmEntry&
 
 // ---- softmax normaliser and q's sum of a node, per slice -------------------------
 // Running maximum and sum of exp((x - m) / T); -inf logits add nothing, NaN
-// ones are flagged (fmaxf skips them).  Eight elements a thread at a time: all
-// loads first, one rescale per eight, one exponential per element.  Thread 0
-// gets the slice's (maximum, sum, q sum, NaN flag); red: 4 floats per wave.
+// ones are flagged (fmaxf skips them).  Every thread gets the slice's (maximum,
+// sum, q sum, NaN flag).
+// The order of these operations is part of the result: a token of the tail has
+// about 1e-7 of the mass, which is the rounding of the sums that a draw is
+// compared with, so another grouping (eight elements per rescale, or the
+// normaliser's partials in the place of the slice's sum of p) moves about one
+// emitted token in 600 to a neighbour.
 template <bool VEC, bool Q>
 __device__ __forceinline__ float4 slice_norm(const float* lg, const float* qd, int lo, int hi, float inv_t,
-                                             float4* red) {
-  const int tid = threadIdx.x;
+                                             float* red) {
   float m = -INFINITY, se = 0.f, sq = 0.f;
-  bool bad = false;
-  for (int base = lo; base < hi; base += 8 * SA_THREADS) {  // uniform
-    float x[8], y[8];
-    if constexpr (VEC) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int at = base + 4 * (tid + h * SA_THREADS);
-        const bool in = at < hi;  // slices start and end on multiples of 4
-        const float4 xv = in ? *reinterpret_cast<const float4*>(lg + at)
-                             : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        const float4 yv = Q && in ? *reinterpret_cast<const float4*>(qd + at) : make_float4(0.f, 0.f, 0.f, 0.f);
-        x[4 * h] = xv.x; x[4 * h + 1] = xv.y; x[4 * h + 2] = xv.z; x[4 * h + 3] = xv.w;
-        y[4 * h] = yv.x; y[4 * h + 1] = yv.y; y[4 * h + 2] = yv.z; y[4 * h + 3] = yv.w;
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int at = base + tid + u * SA_THREADS;
-        x[u] = at < hi ? lg[at] : -INFINITY;
-        y[u] = Q && at < hi ? qd[at] : 0.f;
-      }
-    }
-    float mn = m;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      mn = fmaxf(mn, x[u]);
-      bad |= x[u] != x[u];
-      sq += y[u];
-    }
-    if (mn > m) se *= expf((m - mn) * inv_t);
+  int bad = 0;
+  auto f = [&](float x, float y) {
+    sq += y;
+    bad |= x != x;
+    const float mn = fmaxf(m, x);
+    se = (mn == m ? se : se * expf((m - mn) * inv_t)) + (x > -INFINITY ? expf((x - mn) * inv_t) : 0.f);
     m = mn;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) se += x[u] > -INFINITY ? expf((x[u] - mn) * inv_t) : 0.f;
-  }
-  const float mw = wave_max(m);
-  const float sw = wave_sum(m > -INFINITY ? se * expf((m - mw) * inv_t) : 0.f);
-  const float qw = wave_sum(sq);
-  const float bw = wave_max(bad ? 1.f : 0.f);
-  __syncthreads();
-  if ((tid & 63) == 0) red[tid >> 6] = make_float4(mw, sw, qw, bw);
-  __syncthreads();
-  float4 r = red[0];
-  for (int w = 1; w < SA_THREADS / 64; ++w) r.x = fmaxf(r.x, red[w].x);
-  r.y = 0.f;
-  for (int w = 0; w < SA_THREADS / 64; ++w) r.y += red[w].x > -INFINITY ? red[w].y * expf((red[w].x - r.x) * inv_t) : 0.f;
-  for (int w = 1; w < SA_THREADS / 64; ++w) {
-    r.z += red[w].z;
-    r.w = fmaxf(r.w, red[w].w);
-  }
-  return r;
+  };
+  for_slice<VEC, Q>(lg, qd, lo, hi, f);
+  const float mb = block_max(m, red);
+  const float seb = block_sum(m > -INFINITY ? se * expf((m - mb) * inv_t) : 0.f, red);
+  const float sqb = block_sum(sq, red);
+  const float badb = block_max((float)bad, red);
+  return make_float4(mb, seb, sqb, badb);
 }
 
 template <bool VEC>
 __global__ __launch_bounds__(SA_THREADS) void sampled_norm_kernel(SampledArgs a, int nslice) {
-  __shared__ float4 red[SA_THREADS / 64];
+  __shared__ float red[8];
   const SampScratch sc = sa_carve(a.scratch, a.scratch_batch, a.max_tree, nslice);
   const int s = blockIdx.x, row = a.order[blockIdx.y], V = a.vocab;
   const float* lg = a.logits + (size_t)row * V;
@@ -373,7 +353,7 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_step_kernel(SampledArgs a,
 // ---- the walk and the final node's state (one wave; every workgroup alike) -------
 struct WalkEnd {
   int node, L, nan, pathv;  // pathv: this lane's path entry (lane < L)
-  bool leaf;                // q given and the final node has no children: its partials are the draw launch's
+  bool leaf;                // q given and the final node has no children
   SampState st;             // final node: state after all its children's rejections
   RmEntry e;                // this lane's rejected-token entry of the final node
 };
@@ -432,7 +412,7 @@ __device__ __forceinline__ WalkEnd walk_tree_point_mass(const SampledArgs& a, co
   }
 }
 
-// LEAF: a leaf's partials are there (the draw launch has written them).
+// LEAF: a leaf's partials are there (sampled_leaf_norm_kernel has written them).
 template <bool LEAF>
 __device__ __forceinline__ WalkEnd walk_tree(const SampledArgs& a, const SampScratch& sc, int nslice, int b) {
   if (!a.q) return walk_tree_point_mass(a, sc, nslice, b);
@@ -487,35 +467,45 @@ __device__ __forceinline__ WalkEnd walk_tree(const SampledArgs& a, const SampScr
   return w;
 }
 
-// ---- residual sums of every tree's final node, per slice -------------------------
+// ---- softmax partials of the leaf a tree's walk ends at ---------------------------
 template <bool VEC>
-__global__ __launch_bounds__(SA_THREADS) void sampled_draw_sums_kernel(SampledArgs a, int nslice) {
+__global__ __launch_bounds__(SA_THREADS) void sampled_leaf_norm_kernel(SampledArgs a, int nslice) {
   __shared__ float red[8];
-  __shared__ float4 nred[SA_THREADS / 64];
-  __shared__ SampState sh_st;
-  __shared__ int sh_node, sh_nan, sh_leaf;
-  __shared__ RmEntry rml[SA_RM];
+  __shared__ int sh_leaf;  // its node, -1: the walk ends elsewhere
   const SampScratch sc = sa_carve(a.scratch, a.scratch_batch, a.max_tree, nslice);
   const int s = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.vocab;
   if (tid < 64) {
     const WalkEnd w = walk_tree<false>(a, sc, nslice, b);
+    if (tid == 0) sh_leaf = w.leaf ? w.node : -1;
+  }
+  __syncthreads();
+  if (sh_leaf < 0) return;  // uniform
+  const size_t fr = (size_t)b * a.max_tree + sh_leaf;
+  int lo, hi;
+  slice_range(V, nslice, s, lo, hi);
+  const float4 r = slice_norm<VEC, false>(a.logits + fr * V, nullptr, lo, hi, a.inv_t, red);
+  if (tid == 0) sc.npart[fr * nslice + s] = r;
+}
+
+// ---- residual sums of every tree's final node, per slice -------------------------
+template <bool VEC>
+__global__ __launch_bounds__(SA_THREADS) void sampled_draw_sums_kernel(SampledArgs a, int nslice) {
+  __shared__ float red[8];
+  __shared__ SampState sh_st;
+  __shared__ int sh_node, sh_nan;
+  __shared__ RmEntry rml[SA_RM];
+  const SampScratch sc = sa_carve(a.scratch, a.scratch_batch, a.max_tree, nslice);
+  const int s = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.vocab;
+  if (tid < 64) {
+    const WalkEnd w = walk_tree<true>(a, sc, nslice, b);
     if (tid == 0) {
       sh_st = w.st;
       sh_node = w.node;
       sh_nan = w.nan;
-      sh_leaf = w.leaf;
     }
     rml[tid] = w.e;
   }
   __syncthreads();
-  if (sh_leaf) {  // uniform
-    const size_t fr = (size_t)b * a.max_tree + sh_node;
-    int lo, hi;
-    slice_range(V, nslice, s, lo, hi);
-    const float4 r = slice_norm<VEC, false>(a.logits + fr * V, nullptr, lo, hi, a.inv_t, nred);
-    if (tid == 0) sc.npart[fr * nslice + s] = r;
-    return;
-  }
   float g = 0.f;
   if (!sh_nan) {
     const SampState st = sh_st;
@@ -555,11 +545,7 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_pick_kernel(SampledArgs a,
     w = walk_tree<true>(a, sc, nslice, b);
     rml[tid] = w.e;
     // inclusive scan of the slice sums, in slice order
-    float ps = tid < nslice && !w.leaf ? sc.dpart[(size_t)b * nslice + tid] : 0.f;
-    if (w.leaf && tid < nslice) {  // the sum of p over a slice, from its softmax partials
-      const float4 pp = sc.npart[(row0 + w.node) * nslice + tid];
-      ps = pp.x > -INFINITY ? pp.y * expf((pp.x - w.st.M) * a.inv_t) * w.st.inv_z : 0.f;
-    }
+    const float ps = tid < nslice ? sc.dpart[(size_t)b * nslice + tid] : 0.f;
     float inc = ps;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -654,6 +640,7 @@ static void launch_all(const SampledArgs& a, const int* rows_with, int max_child
   for (int k = 0, base = 0, prev = 0; k < steps; prev = base, base += rows_with[++k])
     hipLaunchKernelGGL(sampled_step_kernel<VEC>, dim3(ns, rows_with[k + 1]), dim3(SA_THREADS), 0, s, a, ns, k, base,
                        prev);
+  if (a.q) hipLaunchKernelGGL(sampled_leaf_norm_kernel<VEC>, dim3(ns, a.batch), dim3(SA_THREADS), 0, s, a, ns);
   hipLaunchKernelGGL(sampled_draw_sums_kernel<VEC>, dim3(ns, a.batch), dim3(SA_THREADS), 0, s, a, ns);
   hipLaunchKernelGGL(sampled_pick_kernel<VEC>, dim3(a.batch), dim3(SA_THREADS), 0, s, a, ns);
 }
