@@ -276,7 +276,13 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const uint16_t* __rest
   const int k = s * 64 + 32 * gg + 8 * j;
   ok = ok && k < K;
   u32x4 v = zero_u4();
-  if (ok) v = *reinterpret_cast<const u32x4*>(src + row * K + k);
+  if (ok && K % 8 == 0) {
+    v = *reinterpret_cast<const u32x4*>(src + row * K + k);
+  } else if (ok) {  // rows of any length (a draft's fusion width): the last piece ends inside the row
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (k + e < K) v[e / 2] |= (uint32_t)src[row * K + k + e] << (e % 2 * 16);
+  }
   *reinterpret_cast<u32x4*>(dst + i * 8) = v;
 }
 

@@ -40,6 +40,21 @@ __device__ __forceinline__ void ks_merge(f32x16 (&acc)[NB][MB], float* red, int 
   }
 }
 
+// Columns n .. n + 3 (n a multiple of 4) of an output row of N: as one store, or
+// where rows of N values are no whole number of 16-byte groups (a vocabulary or
+// a fusion width that is no multiple of 4) one by one, since the row's last group
+// would reach into the next row, or past the caller's buffer.
+__device__ __forceinline__ void store_cols(float* row, int n, int N, float x, float y, float z, float w) {
+  if (N % 4 == 0) {  // uniform
+    if (n < N) *reinterpret_cast<float4*>(row + n) = make_float4(x, y, z, w);
+    return;
+  }
+  if (n < N) row[n] = x;
+  if (n + 1 < N) row[n + 1] = y;
+  if (n + 2 < N) row[n + 2] = z;
+  if (n + 3 < N) row[n + 3] = w;
+}
+
 // The epilogues, every wave for its own NB column blocks of the 32 MB rows from row0.
 template <int EPI, int NB, int WN, int MB>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[NB][MB], int e, int row0, int wg,
@@ -58,9 +73,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[N
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
           const int n = ((wg * WN + wc) * NB + b) * 32 + 8 * rg + 4 * g;
-          if (n < a.N)
-            *reinterpret_cast<float4*>(out + n) = make_float4(acc[b][mb][4 * rg], acc[b][mb][4 * rg + 1],
-                                                              acc[b][mb][4 * rg + 2], acc[b][mb][4 * rg + 3]);
+          store_cols(out, n, a.N, acc[b][mb][4 * rg], acc[b][mb][4 * rg + 1], acc[b][mb][4 * rg + 2],
+                     acc[b][mb][4 * rg + 3]);
         }
     } else if constexpr (EPI == EPI_SWIGLU) {
       // blocks [0, NB/2) hold gate rows, block b + NB/2 the up rows of block b
@@ -122,9 +136,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[N
 #pragma unroll
           for (int rg = 0; rg < 4; ++rg) {
             const int n = ((wg * WN + wc) * NB + b) * 32 + 8 * rg + 4 * g;
-            if (n < a.N)
-              *reinterpret_cast<float4*>(out + n) = make_float4(acc[b][mb][4 * rg], acc[b][mb][4 * rg + 1],
-                                                                acc[b][mb][4 * rg + 2], acc[b][mb][4 * rg + 3]);
+            store_cols(out, n, a.N, acc[b][mb][4 * rg], acc[b][mb][4 * rg + 1], acc[b][mb][4 * rg + 2],
+                       acc[b][mb][4 * rg + 3]);
           }
       }
     }
