@@ -57,7 +57,7 @@ extern "C" {
 #define GRIFFIN_EORDER (-6)    /* griffin_accept / griffin_read_predictions / griffin_read_features before any step */
 #define GRIFFIN_ENOMEM (-7)    /* device or pinned host allocation failed */
 #define GRIFFIN_EHIP (-8)      /* a HIP runtime call failed; griffin_last_error has the text */
-#define GRIFFIN_ENUMERIC (-9)  /* a NaN appeared in the logits of a valid tree node */
+#define GRIFFIN_ENUMERIC (-9)  /* a NaN appeared in the logits of a valid tree node, or left a draft without candidates */
 
 /* Model shape and limits.  Supported: head_dim 64 or 128; n_q_heads a
  * multiple of n_kv_heads; d_model, n_q_heads*head_dim and d_ff multiples of 8;
@@ -376,7 +376,10 @@ griffin_ctx *griffin_draft_context(griffin_draft *draft);
  * b * max_tree + i, its k most probable next tokens (value descending, lower
  * id first on ties) and their log-probabilities: host topk_tokens, topk_logp
  * [batch * max_tree][k], 1 <= k <= 16 (rows of absent nodes untouched).
- * Synchronises the stream.  Errors as griffin_verify_step, EINVAL. */
+ * Synchronises the stream.  Errors as griffin_verify_step, EINVAL, ENUMERIC (a
+ * node with fewer than k logits that are no NaN, as after a NaN in the
+ * features; the outputs are still written, token -1 and log-probability -inf
+ * for what is missing). */
 int griffin_draft_step(griffin_draft *draft, int32_t batch, const int32_t *prefix_len, const int32_t *n_nodes,
                        const int32_t *tokens, const int32_t *parents, const float *root_features, int32_t k,
                        int32_t *topk_tokens, float *topk_logp);
@@ -405,7 +408,9 @@ int griffin_draft_extend(griffin_draft *draft, int32_t batch, const int32_t *pre
  * [batch], tokens_out and parents_out [batch][max_tree], scores_out (optional)
  * [batch][max_tree] the cumulative log-probabilities (root 0).
  * Errors: EINVAL, ETREE (k, depth or n_total do not fit max_tree/max_depth),
- * and those of griffin_draft_step. */
+ * and those of griffin_draft_step (ENUMERIC: the outputs are still written;
+ * nodes without a token hold -1 and score -inf, and sequences whose features
+ * are finite keep their trees). */
 int griffin_draft_tree(griffin_draft *draft, int32_t batch, const int32_t *prefix_len, const int32_t *root_tokens,
                        const float *root_features, int32_t k, int32_t depth, int32_t n_total,
                        int32_t *n_nodes_out, int32_t *tokens_out, int32_t *parents_out, float *scores_out);

@@ -37,6 +37,7 @@ hipError_t launch_draft_head(const DraftArgs& a, const StepMeta& meta, const Res
                              hipStream_t s);
 // Top-k (k <= 16) tokens and log-probabilities of the live nodes [first,
 // first + count) of every tree, from logits [rows][ld] (V <= 524288); `work` holds draft_topk_work_bytes(rows, V).
+// A row with fewer than k logits that are no NaN has token -1, log-probability -inf past them.
 size_t draft_topk_work_bytes(int rows, int V);
 hipError_t launch_draft_topk(const float* logits, long long ld, int V, const StepMeta& meta, int rows, int max_tree,
                              int first, int count, int k, int32_t* tok, float* logp, float* work, hipStream_t s);
@@ -69,7 +70,7 @@ struct DraftSelectArgs {
   const uint4* tail_src;    // next pass's fixed metadata (prefix, sizes, positions, depths, split table)
   uint4* tail_dst;
   int tail_words;
-  int32_t* o_nodes;         // last pass: [batch] node counts, [batch][max_tree] tokens, parents, scores
+  int32_t* o_nodes;         // last pass: [batch] node counts (negated where a candidate had no token), [batch][max_tree] tokens, parents, scores
   int32_t* o_tok;
   int32_t* o_par;
   float* o_score;

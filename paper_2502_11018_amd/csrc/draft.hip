@@ -446,9 +446,9 @@ __global__ __launch_bounds__(TM) void draft_topk_merge_kernel(const float* part,
     if (at < k) best[at] = ck[q];
   }
   __syncthreads();
-  if (tid < k) {
-    tok_out[(long long)r * k + tid] = key_id(best[tid]);
-    logp_out[(long long)r * k + tid] = key_value(best[tid]) - lse;
+  if (tid < k) {  // a row with fewer than k logits that are no NaN: token -1 past them
+    tok_out[(long long)r * k + tid] = best[tid] ? key_id(best[tid]) : -1;
+    logp_out[(long long)r * k + tid] = best[tid] ? key_value(best[tid]) - lse : -INFINITY;
   }
 }
 
@@ -538,11 +538,14 @@ __global__ __launch_bounds__(SEL_T) void draft_select_kernel(DraftSelectArgs a) 
   const int f0 = t == 0 ? 0 : 1 + k * (t - 1), nf = (t == 0 ? 1 : k) * k;
   const int c0 = t == 0 ? 0 : k + k * k * (t - 1);  // index of the first fresh candidate
   const long long cb = (long long)b * DRAFT_SEL_MAX, nb = (long long)b * T;
+  int none = 0;  // the sequence has candidates without a token
   for (int q = tid; q < nf; q += SEL_T) {
     const int r = f0 + q / k;
     const long long at = (nb + r) * k + q % k;
-    const double s = (r == 0 ? 0.0 : a.n_score[nb + r]) + (double)a.topk_lp[at];
-    a.c_tok[cb + c0 + q] = a.topk_tok[at];
+    const int tok = a.topk_tok[at];  // -1: no candidate, ranked last
+    const double s = tok < 0 ? -INFINITY : (r == 0 ? 0.0 : a.n_score[nb + r]) + (double)a.topk_lp[at];
+    none |= tok < 0;
+    a.c_tok[cb + c0 + q] = tok;
     a.c_node[cb + c0 + q] = r;
     a.c_score[cb + c0 + q] = s;
     sc[c0 + q] = sel_key(s);
@@ -556,7 +559,7 @@ __global__ __launch_bounds__(SEL_T) void draft_select_kernel(DraftSelectArgs a) 
         const int node = 1 + k * t + rk, r = f0 + q / k;
         a.n_cand[nb + node] = c0 + q;
         a.n_score[nb + node] = a.c_score[cb + c0 + q];
-        a.m_token[nb + node] = a.c_tok[cb + c0 + q];
+        a.m_token[nb + node] = max(a.c_tok[cb + c0 + q], 0);  // the next pass reads this token's embedding
         a.m_parent[nb + node] = r;
         a.m_anc[nb + node] = a.m_anc[nb + r] | (1ull << node);
       }
@@ -567,11 +570,14 @@ __global__ __launch_bounds__(SEL_T) void draft_select_kernel(DraftSelectArgs a) 
   // last pass: the n_total best of all candidates, numbered by depth, then rank
   const int nc = c0 + nf, keep = min(nc, a.n_total);
   for (int q = tid; q < nc; q += SEL_T) {
-    if (q < c0) sc[q] = sel_key(a.c_score[cb + q]);
+    if (q < c0) {
+      sc[q] = sel_key(a.c_score[cb + q]);
+      none |= a.c_tok[cb + q] < 0;
+    }
     dep[q] = q < k ? 1 : 2 + (q - k) / (k * k);
     slot[q] = -1;
   }
-  __syncthreads();
+  none = __syncthreads_or(none);
   for (int q = tid; q < nc; q += SEL_T) {
     const int rk = sel_rank(sc, nc, sc[q], q);
     if (rk < keep) {  // ranks are distinct
@@ -596,7 +602,7 @@ __global__ __launch_bounds__(SEL_T) void draft_select_kernel(DraftSelectArgs a) 
     a.o_score[nb + at + 1] = (float)a.c_score[cb + q];
   }
   if (tid == 0) {
-    a.o_nodes[b] = 1 + keep;
+    a.o_nodes[b] = none ? -(1 + keep) : 1 + keep;
     a.o_tok[nb] = a.m_token[nb];
     a.o_par[nb] = -1;
     a.o_score[nb] = 0.f;

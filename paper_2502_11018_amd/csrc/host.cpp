@@ -1693,6 +1693,10 @@ int griffin_draft_step(griffin_draft* dc, int32_t batch, const int32_t* prefix_l
   memcpy(topk_tokens, dc->topk_tok_host, sizeof(int32_t) * rows * k);
   memcpy(topk_logp, dc->topk_lp_host, sizeof(float) * rows * k);
   c->stepped = false;  // a draft pass has no acceptance result
+  for (int b = 0; b < batch; ++b)
+    for (int j = 0; j < n_nodes[b] * k; ++j)
+      if (topk_tokens[(size_t)b * d.max_tree * k + j] < 0)
+        return set_err(c, GRIFFIN_ENUMERIC, "sequence " + std::to_string(b) + ": NaN in the draft's logits");
   return GRIFFIN_OK;
 }
 
@@ -1835,13 +1839,16 @@ int griffin_draft_tree(griffin_draft* dc, int32_t batch, const int32_t* prefix_l
   const int32_t* o_tok = dc->out_host + d.max_batch;
   const int32_t* o_par = o_tok + MT;
   const float* o_score = reinterpret_cast<const float*>(o_par + MT);
+  bool nan = false;
   for (int b = 0; b < batch; ++b) {
-    const int n = dc->out_host[b];
+    const int n = std::abs(dc->out_host[b]);  // negated: a candidate without a token
+    nan |= dc->out_host[b] < 0;
     n_nodes_out[b] = n;
     memcpy(tokens_out + (size_t)b * T, o_tok + (size_t)b * T, sizeof(int32_t) * n);
     memcpy(parents_out + (size_t)b * T, o_par + (size_t)b * T, sizeof(int32_t) * n);
     if (scores_out) memcpy(scores_out + (size_t)b * T, o_score + (size_t)b * T, sizeof(float) * n);
   }
+  if (nan) return set_err(c, GRIFFIN_ENUMERIC, "NaN in the draft's logits");
   return GRIFFIN_OK;
 }
 

@@ -378,3 +378,50 @@ def test_topk_of_tied_logits(V, k):
             lv = lv.numpy()
             assert tok[0, 0].tolist() in (np.argsort(-lv, kind="stable")[:k].tolist(),
                                           np.argsort(lv, kind="stable")[:k].tolist())
+
+
+def test_nan_features_are_an_error_and_no_token():
+    """A NaN in one sequence's root feature leaves its draft without candidates.
+    That is reported (GRIFFIN_ENUMERIC) with token -1 and score -inf for what is
+    missing; the passes below such a node read the embedding of token 0.  The
+    other sequence keeps its tree, and later calls are unaffected."""
+    import paper_2502_11018_amd as P
+    from paper_2502_11018_amd import _native as N
+    prefix, roots, k, D, total = [37, 70], [5, 17], 4, 4, 12
+    dr = Draft("tiny", 2, prefix)
+    try:
+        feat = dr.feat[:2].cuda()
+        bad = feat.clone()
+        bad[1, 3] = float("nan")
+        say("draft tree: NaN in the second sequence's root feature")
+        ref = dr.dm.tree(prefix, roots, feat, k, D, total)
+        with pytest.raises(P.GriffinError) as ei:
+            dr.dm.tree(prefix, roots, bad, k, D, total)
+        assert ei.value.name == "GRIFFIN_ENUMERIC"
+        n, tok, par, sc = (np.zeros_like(x) for x in ref)
+        i32 = lambda x: np.ascontiguousarray(x, dtype=np.int32)  # noqa: E731
+        p32 = lambda x: x.ctypes.data_as(N.POINTER(N.c_int32))  # noqa: E731
+        pf = lambda x: x.ctypes.data_as(N.POINTER(N.c_float))  # noqa: E731
+        rc = N.lib.griffin_draft_tree(dr.dm.h, 2, p32(i32(prefix)), p32(i32(roots)), N.c_void_p(bad.data_ptr()), k, D,
+                                      total, p32(n), p32(tok), p32(par), pf(sc))
+        assert P.STATUS[rc] == "GRIFFIN_ENUMERIC"
+        assert n.tolist() == [total + 1, total + 1]
+        for got, want in zip((tok, par, sc), ref[1:]):
+            assert np.array_equal(got[0, : n[0]], want[0, : n[0]])
+        assert tok[1, 0] == roots[1] and (tok[1, 1: n[1]] == -1).all() and (sc[1, 1: n[1]] == -np.inf).all()
+        assert all(0 <= par[1, i] < i for i in range(1, n[1]))
+        say("draft step: NaN in the second sequence's root feature")
+        t = gen.Tree(np.asarray([7], np.int32), np.asarray([-1], np.int32))
+        want = dr.dm.step(prefix, [t, t], feat, k)
+        ktok, klp = np.zeros((2, 64, k), np.int32), np.zeros((2, 64, k), np.float32)
+        nn, tk, pr = i32([1, 1]), np.zeros((2, 64), np.int32), np.full((2, 64), -1, np.int32)
+        tk[:, 0] = 7
+        rc = N.lib.griffin_draft_step(dr.dm.h, 2, p32(i32(prefix)), p32(nn), p32(tk), p32(pr),
+                                      N.c_void_p(bad.data_ptr()), k, p32(ktok), pf(klp))
+        assert P.STATUS[rc] == "GRIFFIN_ENUMERIC"
+        assert np.array_equal(ktok[0, 0], want[0][0, 0]) and np.array_equal(klp[0, 0], want[1][0, 0])
+        assert (ktok[1, 0] == -1).all() and (klp[1, 0] == -np.inf).all()
+        say("draft tree after the error")
+        assert all(np.array_equal(a, b) for a, b in zip(dr.dm.tree(prefix, roots, feat, k, D, total), ref))
+    finally:
+        dr.close()
