@@ -530,12 +530,16 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_draw_sums_kernel(SampledAr
 }
 
 // ---- the emitted token: inverse CDF over the final node's residual ---------------
+// The slices' sums, their scan and the scan inside a slice group the same terms
+// differently, so a threshold within rounding of a slice's end can miss every
+// interval of it: the token is then the slice's last one with mass (its first,
+// where the threshold rounded below the slice), never one without.
 template <bool VEC>
 __global__ __launch_bounds__(SA_THREADS) void sampled_pick_kernel(SampledArgs a, int nslice) {
   __shared__ float scan[SA_THREADS];
   __shared__ RmEntry rml[SA_RM];
   __shared__ SampState sh_st;
-  __shared__ int sh_node, sh_nan, pick_s, found;
+  __shared__ int sh_node, sh_nan, pick_s, found, edge;
   __shared__ float pick_thr;
   const SampScratch sc = sa_carve(a.scratch, a.scratch_batch, a.max_tree, nslice);
   const int b = blockIdx.x, tid = threadIdx.x, V = a.vocab;
@@ -554,14 +558,15 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_pick_kernel(SampledArgs a,
     }
     const float total = __shfl(inc, 63, 64);
     const float thr = a.u_final[row0 + w.node] * total;
-    const uint64_t hit = __ballot(tid < nslice && inc > thr);
-    const int si = hit ? __ffsll((unsigned long long)hit) - 1 : -1;
+    const uint64_t mass = __ballot(ps > 0.f), hit = __ballot(ps > 0.f && inc > thr);
+    const int si = hit ? __ffsll((unsigned long long)hit) - 1 : mass ? 63 - __clzll(mass) : -1;
     if (tid == 0) {
       sh_st = w.st;
       sh_node = w.node;
       sh_nan = w.nan;
       pick_s = si;
       found = -1;
+      edge = 0;
     }
     if (si >= 0 && tid == si) pick_thr = thr - (inc - ps);
   }
@@ -603,18 +608,25 @@ __global__ __launch_bounds__(SA_THREADS) void sampled_pick_kernel(SampledArgs a,
       const float excl = tid > 0 ? scan[tid - 1] : 0.f;
       if (v0 < v1 && excl <= thr && thr < scan[tid]) {
         float accum = excl;
-        int pick = v1 - 1;
+        int pick = -1;
         for (int v = v0; v < v1; ++v) {
-          accum += r_at(v);
-          if (accum > thr) {
-            pick = v;
-            break;
-          }
+          const float r = r_at(v);
+          accum += r;
+          if (r > 0.f) pick = v;
+          if (accum > thr) break;
         }
-        found = pick;  // at most one thread's interval holds thr
+        atomicMax(&found, pick);  // one thread's interval holds thr, or by rounding two: the later
       }
       __syncthreads();
-      emitted = found >= 0 ? found : chi - 1;
+      emitted = found;
+      if (emitted < 0) {  // uniform: thr is outside the slice by rounding
+        int at = 0;       // 1 + distance from the end that is not wanted
+        for (int v = v0; v < v1; ++v)
+          if (r_at(v) > 0.f) at = max(at, thr < 0.f ? chi - v : v - clo + 1);
+        atomicMax(&edge, at);
+        __syncthreads();
+        emitted = edge == 0 ? chi - 1 : thr < 0.f ? chi - edge : clo + edge - 1;
+      }
     }
   }
   if (tid < 64) {

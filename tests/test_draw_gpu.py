@@ -88,3 +88,100 @@ def test_tree_draws_keep_their_tokens():
     import paper_2502_11018_amd as P
     print("[gpu-case] tree draws", flush=True)
     assert tree_draws(P, 128256) == TREE
+
+
+# ---- thresholds on slice boundaries ------------------------------------------------
+
+F = np.float32
+
+
+def _slices(V):
+    n = min(64, max(1, (V + 2047) // 2048))
+    chunk = (-(-V // n) + 3) & ~3
+    return [(min(V, s * chunk), min(V, s * chunk + chunk)) for s in range(n)]
+
+
+def _block_sum(x):
+    """A workgroup's sum of its 256 threads' values: butterflies over each wave, then the waves in order."""
+    t = F(0)
+    for w in x.reshape(4, 64):
+        for o in (32, 16, 8, 4, 2, 1):
+            w = w + w[np.arange(64) ^ o]
+        t = F(t + w[0])
+    return t
+
+
+def _scan(x):
+    """Inclusive doubling scan, as a wave and a workgroup do it."""
+    x, o = x.copy(), 1
+    while o < len(x):
+        x[o:] = x[o:] + x[:-o]
+        o *= 2
+    return x
+
+
+def _level_sums(live):
+    """fp32 sums of a row whose live tokens all have p = 1 / n: per slice as the
+    draw's first level adds them (a thread's groups of four), and per slice the
+    scan of its second (a thread's contiguous range)."""
+    p, top, inner = F(1) / F(live.sum()), [], []
+    for lo, hi in _slices(len(live)):
+        x = np.zeros((hi - lo + 1023) // 1024 * 1024, F)
+        x[: hi - lo] = live[lo:hi] * p
+        t = np.zeros(256, F)
+        for grp in x.reshape(-1, 256, 4):
+            for j in range(4):
+                t = t + grp[:, j]
+        top.append(_block_sum(t))
+        per = -(-(hi - lo) // 256)
+        y = np.zeros(256 * per, F)
+        y[: hi - lo] = live[lo:hi] * p
+        c = np.zeros(256, F)
+        for col in y.reshape(256, per).T:
+            c = c + col
+        inner.append(_scan(c))
+    return np.array(top, F), inner
+
+
+@pytest.mark.parametrize("with_q", [True, False])
+def test_a_draw_on_a_slice_boundary_has_mass(with_q):
+    """Rows of equal live tokens, dead (-inf) at both ends of every slice, drawn
+    at u within a few units of rounding of every slice boundary.  Their sums are
+    known to the bit, and for some of these u the threshold lies outside the
+    slice's own scan.  Every emitted token must be live, and the one that u asks
+    for or its neighbour (fp32 sums over n tokens are off by far less than 1 / n)."""
+    import paper_2502_11018_amd as P
+    V = 128256
+    rng = np.random.default_rng(5)
+    live = rng.random(V) < 0.4
+    for lo, hi in _slices(V):
+        live[lo: lo + 5] = False
+        live[hi - 9: hi] = False
+    n = int(live.sum())
+    top, inner = _level_sums(live)
+    inc = np.zeros(64, F)
+    inc[: len(top)] = top
+    inc = _scan(inc)
+    us, outside = [], 0
+    for i in range(len(top) - 1):
+        u = F(inc[i] / inc[63])
+        for _ in range(4):
+            u = np.nextafter(u, F(0), dtype=F)
+        for _ in range(9):
+            us.append(u)
+            for thr in (float(F(u * inc[63])), float(u) * float(inc[63])):  # rounded, or kept in a fused subtraction
+                s = int(np.argmax(inc > F(u * inc[63])))
+                at = F(thr - float(F(inc[s] - top[s])))
+                outside += not 0 <= at < inner[s][-1]
+            u = np.nextafter(u, F(1), dtype=F)
+    assert outside > 20, outside
+    us = np.array(us, F)[:, None]
+    row = torch.from_numpy(np.where(live, F(0), F(-np.inf)))
+    logits = row.cuda().expand(len(us), V).contiguous()
+    tree = gen.Tree(np.zeros(1, np.int32), np.full(1, -1, np.int32))
+    print(f"[gpu-case] draws on slice boundaries q={with_q}: {len(us)} draws, {outside} thresholds outside", flush=True)
+    r = P.accept_sampled_walk([tree] * len(us), logits, logits if with_q else None, us, us, 1.0, 1, 0, V)
+    tok = r.tokens[:, 0]
+    assert live[tok].all(), (us[~live[tok], 0], tok[~live[tok]])
+    want = np.floor(us[:, 0].astype(np.float64) * n).astype(np.int64)
+    assert np.abs(np.cumsum(live)[tok] - 1 - want).max() <= 1
