@@ -61,3 +61,52 @@ def test_launch_forms_match_oracle(hq, hkv, dh, max_tree, nodes):
             n = trees[b].n
             rel = np.abs(lg[row, :n] - ref[b]).max(axis=1) / np.ptp(ref[b], axis=1)
             assert rel.max() <= H.REGRESS_REL_TOL, (seqs, b, rel.max())
+
+
+def test_softmax_denominator_keeps_small_probabilities():
+    """One node and one head over 65536 keys in 16 splits.  The first key of each
+    split dominates (its value is 1, all others 0), every other key has a
+    probability of just under half a unit of rounding beside it.  The output is 1 /
+    denominator.  Added to the running sum key by key, the small ones of the
+    dominant key's lane would all be lost (1.1e-4); a block's 16 as a tree, then the
+    block, is off by at most 128 blocks x 2^-24, and the output's split into
+    two bf16 parts by 2^-17: 1.6e-5 in all."""
+    import paper_2502_11018_amd as P
+    m = replace(SMALL_GQA, name="denominator", n_layers=1, d_model=64, n_q_heads=1, n_kv_heads=1, head_dim=64,
+                d_ff=64, vocab=64, weight_std=0.2)
+    keys, splits = 65536, 16
+    mw = gen.make_weights(m, 5)
+    lay = mw.layers[0]
+    lay["w_qkv"][64:] = 0                       # the node's own key scores 0, its value is 0
+    lay["w_o"].copy_(torch.eye(64))
+    lay["w_down"].zero_()                       # feature = embedding + attention output
+    ow = oracle.OracleWeights(mw)
+    tree = gen.Tree(np.asarray([3], np.int32), np.asarray([-1], np.int32))
+    x = ow.embed(tree.tokens)
+    q = oracle.model.rmsnorm(x, ow.layer(0)["attn_norm"], m.rms_eps) @ ow.layer(0)["w_qkv"][:64].T
+    q = oracle.model.rope(q[:, None, :], np.asarray([[keys]]), m.rope_base)[0, 0]
+    scale = np.log2(np.e) / 8
+
+    def key(score):                             # a bf16 key of about this score (log2 domain), and its exact one
+        k = H.bf16_round(score / scale * q / (q @ q))
+        return k, (q @ k) * scale
+
+    top, s_top = key(60.0)
+    low, s_low = next(kl for kl in (key(s_top - 24.15 + e) for e in np.linspace(-0.4, 0.4, 161))
+                      if 0.85 < 2.0 ** (kl[1] - s_top + 24) < 0.95)
+    K = np.broadcast_to(low, (1, keys, 64)).copy()
+    V = np.zeros((1, keys, 64))
+    K[0, :: keys // splits] = top
+    V[0, :: keys // splits] = 1.0
+    den = 1 + (keys // splits - 1) * 2.0 ** (s_low - s_top)
+    ref = oracle.verify_tree(ow, lambda l: (K, V), tree, keys).hidden[0] - x[0]
+    assert np.abs(ref * den - 1).max() < 1e-9
+    print("[gpu-case] softmax denominator over 65536 keys", flush=True)
+    with P.TreeVerifier(m, mw.to("cuda"), max_batch=1, max_tree=1, max_depth=0, kv_capacity=keys + 64) as v:
+        v.write_prefix(0, 0, torch.from_numpy(K).to(torch.bfloat16).cuda(),
+                       torch.from_numpy(V).to(torch.bfloat16).cuda())
+        v.step([keys], [tree])
+        out = v.features([[0]]).cpu().numpy()[0, 0].astype(np.float64) - x[0]
+    rel = np.abs(out / ref - 1).max()
+    print(f"[gpu-case] softmax denominator off by {rel:.2e}", flush=True)
+    assert rel < 1.6e-5, rel
