@@ -32,12 +32,6 @@ int cdiv(int x, int m) { return (x + m - 1) / m; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Launch of gemm_rows.hip for one step: workgroup tile 64 wm rows x 128 wn
-// columns, `splits` K splits of `len` steps.
-struct RowsLaunch {
-  int wm = 0, wn = 0, splits = 1, len = 0;
-};
-
 // Launch shape of one weight matrix (fixed at init; the packing follows it).
 struct GemmPlan {
   int epi = 0, nb = 1, wn = 4, pf = 4;
@@ -52,40 +46,6 @@ struct GemmPlan {
   PackShape shape{};
   long long elems = 0;  // packed elements of one matrix (one expert)
 };
-
-// Tile shape and K splits of a gemm_rows launch over m_tiles row tiles: the
-// least estimated time.  Measured per K step and 64 x 128 tile of a workgroup
-// (Llama-3-8B shapes, 128 to 512 rows): 0.37 us in the 256- and 128-row x 256-column
-// shapes, 0.40 us in the 128-row x 128-column and 0.43 in the 64-row one (more operand bytes per
-// MFMA), in whole rounds of 256 workgroups; 8 us per round for the launch, the
-// ring's fill and the slice merge; partial sums at about 3.3 TB/s for the
-// write and the consumer's read together; and never faster than the weight
-// stream at 4.2 TB/s.
-RowsLaunch plan_rows(int epi, int groups, int ks, int n_cols, int m_tiles) {
-  static const int shapes[4][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 2}};
-  RowsLaunch best;
-  double best_t = 1e30;
-  for (const auto& sh : shapes) {
-    const int wm = sh[0], wn = sh[1];
-    const int tiles = cdiv(m_tiles, wm) * (groups / wn);
-    const int most = epi == EPI_STORE ? std::min(16, std::max(1, ks / 4)) : 1;
-    for (int want = 1; want <= most; ++want) {
-      const int len = cdiv(ks, want), splits = cdiv(ks, len);
-      const double step = wm * wn * (wn * wm >= 4 ? 0.37 : wm == 2 ? 0.40 : 0.43);  // us per K step
-      double t = cdiv(tiles * splits, 256) * (len * step + 8.0);
-      t = std::max(t, (double)groups * ks * 16384.0 / 4.2e6);
-      if (epi == EPI_STORE) t += splits * m_tiles * 64.0 * n_cols * 4.0 / 3.3e6;
-      if (t < best_t) {
-        best_t = t;
-        best.wm = wm;
-        best.wn = wn;
-        best.splits = splits;
-        best.len = len;
-      }
-    }
-  }
-  return best;
-}
 
 // m_tiles: the most 64-row tiles a step of the context can have.  With one
 // tile the weight stream bounds the GEMMs (gemm.hip); with several the matrix
@@ -104,7 +64,7 @@ GemmPlan plan_gemm(int epi, int n_out, int K, int experts = 1, int m_tiles = 1) 
     p.ks_pad = p.ks;
     p.shape = PackShape{p.nb, p.wn, 1, p.ks, groups, epi == EPI_SWIGLU ? 1 : 0, n_out, 1};
     p.elems = packed_elems(p.shape);
-    for (int t = 1; t <= m_tiles; ++t) p.rows_for.push_back(plan_rows(epi, groups, p.ks, n_out, t));
+    for (int t = 1; t <= m_tiles; ++t) p.rows_for.push_back(plan_rows(epi == EPI_STORE, groups, p.ks, n_out, t));
     return p;
   }
   int splits = 1;

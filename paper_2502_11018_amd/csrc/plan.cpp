@@ -1,6 +1,6 @@
 // Host-only planning of a verification step: tree validation and metadata,
-// the prefix-attention split table, the model-shape checks and the work list
-// of the stochastic acceptance.  Plain C++ with no device code, so it also
+// the prefix-attention split table, the GEMM launches over several row tiles, the
+// model-shape checks and the work list of the stochastic acceptance.  Plain C++ with no device code, so it also
 // builds into a CPU test program under the address and undefined-behaviour
 // sanitizers.
 
@@ -95,6 +95,42 @@ int merge_slots(const int32_t* nsplit, int batch, int sp) {
   int slots = 1;
   while (slots < most) slots *= 2;
   return std::min(slots, sp);
+}
+
+static int cdiv(int x, int m) { return (x + m - 1) / m; }
+
+// Tile shape and K splits of a gemm_rows launch over m_tiles row tiles: the
+// least estimated time.  Measured per K step and 64 x 128 tile of a workgroup
+// (Llama-3-8B shapes, 128 to 512 rows): 0.37 us in the 256- and 128-row x 256-column
+// shapes, 0.40 us in the 128-row x 128-column and 0.43 in the 64-row one (more operand bytes per
+// MFMA), in whole rounds of 256 workgroups; 8 us per round for the launch, the
+// ring's fill and the slice merge; partial sums at about 3.3 TB/s for the
+// write and the consumer's read together; and never faster than the weight
+// stream at 4.2 TB/s.
+RowsLaunch plan_rows(bool store, int groups, int ks, int n_cols, int m_tiles) {
+  static const int shapes[4][2] = {{4, 2}, {2, 2}, {2, 1}, {1, 2}};
+  RowsLaunch best;
+  double best_t = 1e30;
+  for (const auto& sh : shapes) {
+    const int wm = sh[0], wn = sh[1];
+    const int tiles = cdiv(m_tiles, wm) * (groups / wn);
+    const int most = store ? std::min(16, std::max(1, ks / 4)) : 1;
+    for (int want = 1; want <= most; ++want) {
+      const int len = cdiv(ks, want), splits = cdiv(ks, len);
+      const double step = wm * wn * (wn * wm >= 4 ? 0.37 : wm == 2 ? 0.40 : 0.43);  // us per K step
+      double t = cdiv(tiles * splits, 256) * (len * step + 8.0);
+      t = std::max(t, (double)groups * ks * 16384.0 / 4.2e6);
+      if (store) t += splits * m_tiles * 64.0 * n_cols * 4.0 / 3.3e6;
+      if (t < best_t) {
+        best_t = t;
+        best.wm = wm;
+        best.wn = wn;
+        best.splits = splits;
+        best.len = len;
+      }
+    }
+  }
+  return best;
 }
 
 int validate_desc(const griffin_model_desc* d, std::string* why) {

@@ -1,6 +1,7 @@
 // Host-only planning of a verification step (no device code): tree
-// validation and metadata, the prefix-attention split table, model-shape
-// checks and the stochastic acceptance's work list.
+// validation and metadata, the prefix-attention split table, the GEMM launches
+// over several row tiles, model-shape checks and the stochastic acceptance's
+// work list.
 #pragma once
 
 #include <stdint.h>
@@ -29,6 +30,16 @@ void attn_split_plan(int batch, const int32_t* prefix_len, const int32_t* n_node
 // batch rounded up to a power of two (few distinct values, so few captured
 // step graphs), at most sp.
 int merge_slots(const int32_t* nsplit, int batch, int sp);
+
+// Launch of gemm_rows.hip for one step: workgroup tile 64 wm rows x 128 wn
+// columns, `splits` K splits of `len` steps.
+struct RowsLaunch {
+  int wm = 0, wn = 0, splits = 1, len = 0;
+};
+
+// The launch over m_tiles 64-row tiles of a matrix of `groups` 128-column groups
+// and ks K steps; store: it writes partial sums of n_cols columns and may split K.
+RowsLaunch plan_rows(bool store, int groups, int ks, int n_cols, int m_tiles);
 
 // GRIFFIN_OK or GRIFFIN_ESHAPE for a model shape the kernels do not support.
 int validate_desc(const griffin_model_desc* d, std::string* why);

@@ -7,6 +7,8 @@
 //       -> tab[batch*splits*4] nsplit[batch]    (prefix-attention split table)
 //   D n_layers d_model hq hkv dh d_ff vocab experts top_k eps base mb mt md cap
 //       -> rc                                   (model-shape validation)
+//   R store groups ks n_cols m_tiles
+//       -> wm wn splits len                     (tile shape and K splits over several row tiles)
 //   Q batch max_tree nodes[batch] par[batch*max_tree] tok[batch*max_tree]
 //       -> order | rows_with | step_child | step_token
 #include <cstdio>
@@ -73,6 +75,11 @@ int main() {
           d.kv_capacity;
       std::string why;
       std::cout << validate_desc(&d, &why) << '\n';
+    } else if (op == 'R') {
+      int store, groups, ks, n_cols, m_tiles;
+      in >> store >> groups >> ks >> n_cols >> m_tiles;
+      const RowsLaunch r = plan_rows(store != 0, groups, ks, n_cols, m_tiles);
+      std::cout << r.wm << ' ' << r.wn << ' ' << r.splits << ' ' << r.len << '\n';
     } else if (op == 'Q') {
       int batch, mt;
       in >> batch >> mt;

@@ -22,13 +22,18 @@ DENSE = replace(SMALL_GQA, name="half-dense", n_layers=2, vocab=1100)
 MOE = replace(DENSE, name="half-moe", n_experts=2, top_k=2)
 # one of four kept: counts on either side of the edge in one launch
 MOE_MIXED = replace(DENSE, name="half-moe-mixed", n_experts=4, top_k=1)
+# widths of the models in use: the deeper pipelines, and two K slices a workgroup in
+# the down projection, that short K ranges do not take
+WIDE = replace(DENSE, name="half-wide", n_layers=1, d_model=4096, n_q_heads=32, n_kv_heads=8, d_ff=14336)
+WIDE_MOE = replace(WIDE, name="half-wide-moe", n_experts=2, top_k=2)
+WIDE_MIXED = replace(WIDE, name="half-wide-moe-mixed", n_experts=4, top_k=1)
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("m", [DENSE, MOE, MOE_MIXED], ids=lambda m: m.name)
+@pytest.mark.parametrize("m", [DENSE, MOE, MOE_MIXED, WIDE, WIDE_MOE, WIDE_MIXED], ids=lambda m: m.name)
 def test_first_nodes_keep_their_bits(m, bf16):
     import paper_2502_11018_amd as P
-    mw = gen.make_weights(m, 7)
+    mw = gen.make_weights(m, 7, device="cuda")
     kv = H.prefix_kv_synthetic(m, 0, PREFIX, 7)
     full = gen.random_tree((7, 14, 21, 21), m.vocab, 4)[0]
     assert full.n == 64

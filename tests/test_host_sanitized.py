@@ -181,3 +181,30 @@ def test_sampled_work_list_matches_python(driver):
                 child.append(kids[r][k])
                 token.append(int(tok[r // mt, kids[r][k]]))
         assert parts == [order, rows_with, child, token]
+
+
+def _rows_plan(driver, m, store, n_out, rows, K, tiles):
+    groups = -(-(-(-rows // 128)) // 2) * 2
+    out = driver([f"R {int(store)} {groups} {-(-K // 64)} {n_out} {t}" for t in tiles])
+    return [tuple(int(x) for x in line.split()) for line in out]
+
+
+def test_row_tile_launches(driver):
+    """Every launch covers K once with no empty split, and the batches that
+    tests/test_rows_gpu.py runs take all four tile shapes, in the matrices that
+    split K and in gate/up."""
+    from tests.test_rows_gpu import MODEL, WIDE, WIDE_BATCHES
+    shapes = {(4, 2), (2, 2), (2, 1), (1, 2)}
+    for m, tiles in ((WIDE, WIDE_BATCHES), (MODEL, range(1, 9)), (WORKLOADS["llama2-7b"].model, range(1, 33))):
+        d, f, w = m.d_model, m.d_ff, m.n_q_heads * m.head_dim
+        store = [p for n_out, K in ((m.qkv_rows, d), (d, w), (d, f))
+                 for p in zip(_rows_plan(driver, m, True, n_out, n_out, K, tiles), [K] * len(tiles))]
+        plain = [p for n_out, rows in ((f, 2 * f), (m.vocab, m.vocab))
+                 for p in zip(_rows_plan(driver, m, False, n_out, rows, d, tiles), [d] * len(tiles))]
+        for (wm, wn, splits, length), K in store + plain:
+            ks = -(-K // 64)
+            assert (wm, wn) in shapes and 1 <= splits <= 16 and (splits - 1) * length < ks <= splits * length
+        assert all(p[2] == 1 for p, _ in plain)
+        if m is WIDE:
+            assert {p[:2] for p, _ in store} == shapes
+            assert {p[:2] for p, _ in plain[: len(tiles)]} == shapes

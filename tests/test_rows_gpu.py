@@ -1,6 +1,9 @@
 """The GEMMs over several 64-row tiles (csrc/gemm_rows.hip) against the fp64
-oracle: every number of row tiles a context can run, which is what the tile
-shape, the K splits and the last tile's padding depend on."""
+oracle.  The tile shape, the K splits and the last tile's padding depend on
+the matrix and on the step's number of row tiles: a narrow model with a wide
+head over every tile count of a context (its other matrices keep one shape), and
+the widths of the models in use over the counts that give every shape to the
+projections and to gate/up."""
 
 from dataclasses import replace
 
@@ -20,6 +23,10 @@ pytestmark = pytest.mark.gpu
 # end inside a column tile and a K step
 MODEL = replace(SMALL_GQA, name="rows", n_layers=1, vocab=100004)
 PREFIX = 37
+
+# tests/test_host_sanitized.py checks that these batches take all four tile shapes
+WIDE = replace(MODEL, name="rows-wide", d_model=4096, n_q_heads=32, n_kv_heads=8, d_ff=14336, vocab=1100)
+WIDE_BATCHES = (1, 2, 3, 4, 5, 8, 9, 12)
 
 
 @pytest.fixture(scope="module")
@@ -62,3 +69,36 @@ def test_every_tile_count_matches_oracle(model, max_tree, batches):
         for b, ref in refs.items():
             rel = np.abs(lg[b, : trees[b].n] - ref).max(axis=1) / np.ptp(ref, axis=1)
             assert rel.max() <= H.LOGIT_REL_TOL, (b, rel.max())
+
+
+def test_every_tile_shape_at_wide_matrices():
+    """One context, all batches, both activation precisions.  The K splits change
+    with the batch, so a sequence's bits may; its logits stay within the bound."""
+    import paper_2502_11018_amd as P
+    m, T, top = WIDE, 64, max(WIDE_BATCHES)
+    mw = gen.make_weights(m, 3, device="cuda")
+    ow, kv = oracle.OracleWeights(mw.to("cpu"), cache=True), H.prefix_kv_synthetic(m, 0, PREFIX, 3)
+    trees = [gen.random_tree((4, 8, 8, 8) if b % 2 else (10, 17, 18, 18), m.vocab, 50 + b)[0] for b in range(top)]
+    refs = {}
+    for b in (0, 1, 4, 8, 11):
+        print(f"[gpu-case] rows wide: oracle of sequence {b}", flush=True)
+        refs[b] = oracle.verify_tree(ow, kv.fn(), trees[b], PREFIX).logits
+    with P.TreeVerifier(m, mw, max_batch=top, max_tree=T, max_depth=8, kv_capacity=128) as v:
+        for b in range(top):
+            v.write_prefix(0, b, torch.from_numpy(kv.K[0]).to(torch.bfloat16).cuda(),
+                           torch.from_numpy(kv.V[0]).to(torch.bfloat16).cuda())
+        for bf16, tol in ((False, H.REGRESS_REL_TOL), (True, H.LOGIT_REL_TOL)):
+            v.set_bf16_activations(bf16)
+            for B in WIDE_BATCHES:
+                print(f"[gpu-case] rows wide batch {B} bf16 {bf16}", flush=True)
+                out = torch.full((B * T, m.vocab), float("nan"), device="cuda")
+                v.step([PREFIX] * B, trees[:B], out)
+                pred = v.predictions()
+                lg = out.view(B, T, -1).cpu().numpy()
+                for b, ref in refs.items():
+                    if b >= B:
+                        continue
+                    n = trees[b].n
+                    rel = np.abs(lg[b, :n] - ref).max(axis=1) / np.ptp(ref, axis=1)
+                    assert rel.max() <= tol, (B, b, bf16, rel.max())
+                    assert np.array_equal(pred[b, :n], lg[b, :n].argmax(axis=1)), (B, b)
