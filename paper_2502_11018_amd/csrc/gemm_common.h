@@ -129,7 +129,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[N
         a.pidx[orow * a.ld_part + part] = bidx;
         a.pnan[orow * a.ld_part + part] = nan_cnt;
       }
-      if (a.logits && orow < a.logit_rows) {
+      if (a.logits && orow < a.logit_rows && orow % a.max_tree < a.n_nodes[orow / a.max_tree]) {
         float* out = a.logits + orow * a.ld_logits;
 #pragma unroll
         for (int b = 0; b < NB; ++b)

@@ -90,9 +90,10 @@ struct GemmArgs {
   int32_t* pidx;
   int32_t* pnan;
   int ld_part;
-  float* logits;             // optional fp32 [rows][ld_logits], rows < logit_rows
-  long long ld_logits;
-  int logit_rows;
+  float* logits;             // optional fp32 [rows][ld_logits]: written for rows < logit_rows of live nodes, node
+  long long ld_logits;       // r % max_tree of sequence r / max_tree live below n_nodes
+  int logit_rows, max_tree;
+  const int32_t* n_nodes;
   // per-launch timing (null when not timed): [0] = ~(earliest workgroup
   // start), [1] = latest wave end, device wall clock; both start at 0
   unsigned long long* stamp;

@@ -510,6 +510,8 @@ int enqueue_pass(griffin_ctx* c, float* logits_out) {
     a.logits = logits_out;
     a.ld_logits = d.vocab;
     a.logit_rows = rows;
+    a.max_tree = d.max_tree;
+    a.n_nodes = c->meta.n_nodes;
     a.stamp = stamp_slot(c, GRIFFIN_KC_LM_HEAD);
     LAUNCH(GRIFFIN_KC_LM_HEAD, launch_plan(c->p_lm, a, 1, s));
   }
