@@ -1652,13 +1652,15 @@ int griffin_draft_step(griffin_draft* dc, int32_t batch, const int32_t* prefix_l
   HIP_TRY(c, hipMemcpyAsync(dc->topk_lp_host, dc->topk_lp, sizeof(float) * rows * k, hipMemcpyDeviceToHost,
                             c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  memcpy(topk_tokens, dc->topk_tok_host, sizeof(int32_t) * rows * k);
-  memcpy(topk_logp, dc->topk_lp_host, sizeof(float) * rows * k);
   c->stepped = false;  // a draft pass has no acceptance result
-  for (int b = 0; b < batch; ++b)
-    for (int j = 0; j < n_nodes[b] * k; ++j)
-      if (topk_tokens[(size_t)b * d.max_tree * k + j] < 0)
-        return set_err(c, GRIFFIN_ENUMERIC, "sequence " + std::to_string(b) + ": NaN in the draft's logits");
+  bool nan = false;
+  for (int b = 0; b < batch; ++b) {
+    const size_t at = (size_t)b * d.max_tree * k, n = (size_t)n_nodes[b] * k;
+    memcpy(topk_tokens + at, dc->topk_tok_host + at, sizeof(int32_t) * n);
+    memcpy(topk_logp + at, dc->topk_lp_host + at, sizeof(float) * n);
+    for (size_t j = 0; j < n; ++j) nan |= topk_tokens[at + j] < 0;
+  }
+  if (nan) return set_err(c, GRIFFIN_ENUMERIC, "NaN in the draft's logits");
   return GRIFFIN_OK;
 }
 
