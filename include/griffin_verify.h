@@ -131,6 +131,11 @@ int griffin_verify_init(const griffin_model_desc *desc, const griffin_weights *w
  * The pass writes the trees' K/V into cache slots [prefix_len, prefix_len+n)
  * of each sequence, then runs the acceptance walk on the device.  The host
  * arrays may be reused as soon as the call returns.
+ * The same step of one context gives the same bits every time.  What else is in
+ * the batch can change a sequence's last bits: in a context of more than 64
+ * rows (max_batch * max_tree) the K splits of the projections follow the
+ * step's number of 64-row tiles (batch * max_tree), and with several sequences
+ * the attention's key splits follow their prefix lengths.
  * Errors: EINVAL, ETREE, ETOKEN, ECAPACITY (nothing launched), EHIP. */
 int griffin_verify_step(griffin_ctx *ctx, int32_t batch, const int32_t *prefix_len,
                         const int32_t *n_nodes, const int32_t *tokens, const int32_t *parents,

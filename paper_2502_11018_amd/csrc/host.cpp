@@ -772,7 +772,9 @@ int griffin_verify_init(const griffin_model_desc* desc, const griffin_weights* w
     // every CU with fewer (the ring's LDS holds two), at least four 32-key
     // blocks per split at full capacity (with two, a 1024-key Llama-2-7B step
     // paid 1.6 us more in the merge and 0.4 in the attention) and at most 16
-    // splits
+    // splits.  The bound is by capacity: a shorter prefix has fewer blocks in
+    // each of them, and of several sequences' splits dealt by prefix length
+    // (attn_split_plan) one may hold as few as two
     const AttnShape sh = attn_shape(d.n_q_heads / d.n_kv_heads, d.max_tree);
     const int units = d.max_batch * d.n_kv_heads * sh.per_unit;
     const int by_par = cdiv(sh.nw == 4 ? 256 : 512, units);

@@ -54,7 +54,7 @@ int prepare_tree(int32_t n, const int32_t* tokens, const int32_t* parents, int32
 // Prefix-attention work of one step: batch * splits units, each sequence at
 // least one and at most min(sp, blocks / 2) (blocks = 32-key blocks of its
 // prefix), the rest dealt one at a time to the sequence with the most blocks
-// per split (ties: the lower index).  A sequence's result depends on the
+// per split (ties: the lower index).  A sequence's attention depends on the
 // batch only through its split count.  tab [batch * splits][4]: (b | split <<
 // 16, splits of b, prefix_len, n_nodes), b = -1 for units left unused;
 // nsplit [batch].

@@ -216,7 +216,7 @@ def test_empty_prefix_matches_oracle():
 
 def test_scores_past_the_attention_cap_match_oracle():
     """Prefix keys after the first 32 are scaled by 2^14, so inside the first
-    key split (two 32-key blocks: 1024 keys over 16 splits) the second block's
+    key split (four 32-key blocks: 1024 keys over 8 splits) the later blocks'
     scores exceed the first block's maximum by thousands of log2 units, far
     past the 2^64 bound the attention kernel allows its unnormalised
     probabilities (they overflow to inf there).  That split is flagged and
